@@ -89,6 +89,111 @@ __device__ __forceinline__ double from_right(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// End-lane values of each wavefront for the row path, double-buffered by the
+// parity of the block's row-path items (one barrier per such item, so a
+// wavefront writing one buffer has passed the barrier that follows every read
+// of it).
+template <typename T>
+struct RowEdges {
+  T v[2][2][kBlock / 64][5];
+};
+
+// The 19 post-stream populations of site (x, y, z) on the row path (all
+// threads of the block call it, `act` or not).  Offsets are 32-bit (the row
+// path is taken only for replicas of fewer than 2^32 / 19 sites): population
+// i of the row (y', z') is at plane(z') + i A + row(y'), with i A folded into
+// the scalar base.
+template <typename T>
+__device__ __forceinline__ void pull_row(const T* __restrict__ sbase, const Geom& g, bool act,
+                                         int x, int y, int z, int lane, int wv, RowEdges<T>& edge,
+                                         int& par, T d[19]) {
+  // populations pulled from x - 1 (c_x = +1) and from x + 1 (c_x = -1)
+  constexpr int kFromLeft[5] = {1, 7, 9, 11, 13};
+  constexpr int kFromRight[5] = {2, 8, 10, 12, 14};
+  const uint32_t A = (uint32_t)g.A;
+  const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
+  const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
+  const uint32_t z0 = (uint32_t)z * 19u * A, zl = (uint32_t)zm * 19u * A,
+                 zh = (uint32_t)zp * 19u * A;
+  const uint32_t r0 = (uint32_t)(y * g.nx + x), rl = (uint32_t)(ym * g.nx + x),
+                 rh = (uint32_t)(yp * g.nx + x);
+  // (plane, row) of each population's source: z - c_z, y - c_y
+  const uint32_t o00 = z0 + r0, o0l = z0 + rl, o0h = z0 + rh;
+  const uint32_t ol0 = zl + r0, olh = zl + rh, oll = zl + rl;
+  const uint32_t oh0 = zh + r0, ohl = zh + rl, ohh = zh + rh;
+  const uint32_t off[19] = {o00, o00, o00, o0l, o0h, ol0, oh0, o0l, o0h, o0h,
+                            o0l, ol0, oh0, oh0, ol0, oll, ohh, ohl, olh};
+  // every population is read once: non-temporal loads keep the stream from
+  // evicting the transfer field and the mark words
+#pragma unroll
+  for (int i = 0; i < 19; ++i)
+    d[i] = act ? __builtin_nontemporal_load(sbase + (size_t)i * A + off[i]) : T(0);
+  // the x shift: rotate by one lane; the end lanes take the neighbouring
+  // wavefront's end value (periodic inside the row of nx/64 wavefronts)
+  if (lane == 63) {
+#pragma unroll
+    for (int j = 0; j < 5; ++j) edge.v[par][0][wv][j] = d[kFromLeft[j]];
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int j = 0; j < 5; ++j) edge.v[par][1][wv][j] = d[kFromRight[j]];
+  }
+  __syncthreads();
+  const int wpr = g.nx >> 6;  // wavefronts per row: 1, 2 or 4
+  const int wl = wv & (wpr - 1), rb = wv - wl;
+  const int wleft = rb + ((wl + wpr - 1) & (wpr - 1));
+  const int wright = rb + ((wl + 1) & (wpr - 1));
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    const T l = from_left(d[kFromLeft[j]]);
+    const T r = from_right(d[kFromRight[j]]);
+    d[kFromLeft[j]] = lane == 0 ? edge.v[par][0][wleft][j] : l;
+    d[kFromRight[j]] = lane == 63 ? edge.v[par][1][wright][j] : r;
+  }
+  par ^= 1;
+}
+
+// The same on the general path with 32-bit offsets inside population i's
+// slab, i A folded into the scalar base (the replica's 19 S entries fit 32
+// bits).
+template <typename T>
+__device__ __forceinline__ void pull_off32(const T* __restrict__ sbase, const Geom& g, int x,
+                                           int y, int z, T d[19]) {
+  const uint32_t A = (uint32_t)g.A;
+  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
+  const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
+  const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
+  const uint32_t z0 = (uint32_t)z * 19u * A, zl = (uint32_t)zm * 19u * A,
+                 zh = (uint32_t)zp * 19u * A;
+  const uint32_t r0 = (uint32_t)(y * g.nx), rl = (uint32_t)(ym * g.nx),
+                 rh = (uint32_t)(yp * g.nx);
+  const uint32_t X0 = (uint32_t)x, Xl = (uint32_t)xm, Xh = (uint32_t)xp;
+  // source (plane, row, column) of each population: z - c_z, y - c_y, x - c_x
+  const uint32_t off[19] = {z0 + r0 + X0, z0 + r0 + Xl, z0 + r0 + Xh, z0 + rl + X0,
+                            z0 + rh + X0, zl + r0 + X0, zh + r0 + X0, z0 + rl + Xl,
+                            z0 + rh + Xh, z0 + rh + Xl, z0 + rl + Xh, zl + r0 + Xl,
+                            zh + r0 + Xh, zh + r0 + Xl, zl + r0 + Xh, zl + rl + X0,
+                            zh + rh + X0, zh + rl + X0, zl + rh + X0};
+  // (plain loads: a shifted run straddles cache lines that the neighbouring
+  // wavefront reads too, so the lines should stay in L2)
+#pragma unroll
+  for (int i = 0; i < 19; ++i) d[i] = sbase[(size_t)i * A + off[i]];
+}
+
+// Whether the replica's population entries have 32-bit offsets.
+__device__ __forceinline__ bool fits_off32(const Geom& g) {
+  return 19ull * (unsigned long long)g.S < (1ull << 32);
+}
+
+// Item of a block: workgroups go to the 8 XCDs in turn and each XCD has its
+// own L2, so on the general path XCD x takes the x-th contiguous range of
+// the work; the lines that the shifted runs of neighbouring items share are
+// then fetched once.
+__device__ __forceinline__ int xcd_first_item() {
+  const int G = gridDim.x, q8 = G / 8, r8 = G % 8, xcd = blockIdx.x % 8;
+  return xcd * q8 + (xcd < r8 ? xcd : r8) + blockIdx.x / 8;
+}
+
 // With Rec, the transfer field and the mark words the step consumes are also
 // copied out for the reverse sweep (the adjoint needs the force density of
 // the step and the set of sites the MD steps touched).
@@ -96,14 +201,7 @@ __device__ __forceinline__ double from_right(double v) {
 // path, 2 per replica (a batch mixing both).
 template <typename T, bool Rec, bool VarC, int Mode>
 __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
-  // populations pulled from x - 1 (c_x = +1) and from x + 1 (c_x = -1)
-  constexpr int kFromLeft[5] = {1, 7, 9, 11, 13};
-  constexpr int kFromRight[5] = {2, 8, 10, 12, 14};
-  // row path: end-lane values of each wavefront, double-buffered by the
-  // parity of the block's row-path items (one barrier per such item, so a
-  // wavefront writing one buffer has passed the barrier that follows every
-  // read of it)
-  __shared__ T edge[2][2][kBlock / 64][5];
+  __shared__ RowEdges<T> edge;
   const int cur = a.clock->cur;
   const long long t = a.clock->t_lb;
   const T* __restrict__ src = a.pop[cur];
@@ -112,17 +210,10 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
   const uint32_t step_hi = (uint32_t)((unsigned long long)t >> 32);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int par = 0;
-  // General path: workgroups go to the 8 XCDs in turn and each XCD has its
-  // own L2, so XCD x takes the x-th contiguous range of the items; the lines
-  // that the shifted runs of neighbouring items share are then fetched once
-  // (measured on 512 replicas of 24-48 sites per edge: reads 1.20x -> 1.03x
-  // the algorithmic bytes).  The row path reads aligned runs and keeps the
-  // plain order.
-  int item0 = blockIdx.x;
-  if (Mode == 0) {
-    const int G = gridDim.x, q8 = G / 8, r8 = G % 8, xcd = blockIdx.x % 8;
-    item0 = xcd * q8 + (xcd < r8 ? xcd : r8) + blockIdx.x / 8;
-  }
+  // general path: XCD-contiguous items (measured on 512 replicas of 24-48
+  // sites per edge: reads 1.20x -> 1.03x the algorithmic bytes).  The row path
+  // reads aligned runs and keeps the plain order.
+  const int item0 = Mode == 0 ? xcd_first_item() : (int)blockIdx.x;
   for (int item = item0; item < a.nitems; item += gridDim.x) {
     // the replica is uniform across the block: keep its constants in scalar
     // registers
@@ -137,75 +228,11 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
     T d[19];
     const bool rows = Mode == 2 ? q.rows != 0 : Mode == 1;
     // general path: 32-bit offsets where the replica's entries allow (uniform)
-    const bool off32 = !rows && 19ull * (unsigned long long)q.g.S < (1ull << 32);
+    const bool off32 = !rows && fits_off32(q.g);
     if (rows) {
-      // aligned loads at this lane's own x.  Offsets are 32-bit here (the
-      // row path is taken only for replicas of fewer than 2^32 / 19 sites):
-      // population i of the row (y', z') is at plane(z') + i A + row(y'),
-      // with i A folded into the scalar base
-      const uint32_t A = (uint32_t)q.g.A;
-      const int ym = y == 0 ? q.g.ny - 1 : y - 1, yp = y == q.g.ny - 1 ? 0 : y + 1;
-      const int zm = z == 0 ? q.g.nz - 1 : z - 1, zp = z == q.g.nz - 1 ? 0 : z + 1;
-      const uint32_t z0 = (uint32_t)z * 19u * A, zl = (uint32_t)zm * 19u * A,
-                     zh = (uint32_t)zp * 19u * A;
-      const uint32_t r0 = (uint32_t)(y * q.g.nx + x), rl = (uint32_t)(ym * q.g.nx + x),
-                     rh = (uint32_t)(yp * q.g.nx + x);
-      // (plane, row) of each population's source: z - c_z, y - c_y
-      const uint32_t o00 = z0 + r0, o0l = z0 + rl, o0h = z0 + rh;
-      const uint32_t ol0 = zl + r0, olh = zl + rh, oll = zl + rl;
-      const uint32_t oh0 = zh + r0, ohl = zh + rl, ohh = zh + rh;
-      const uint32_t off[19] = {o00, o00, o00, o0l, o0h, ol0, oh0, o0l, o0h, o0h,
-                                o0l, ol0, oh0, oh0, ol0, oll, ohh, ohl, olh};
-      // every population is read once per step: non-temporal loads keep the
-      // stream from evicting the transfer field and the mark words
-#pragma unroll
-      for (int i = 0; i < 19; ++i)
-        d[i] = act ? __builtin_nontemporal_load(sbase + (size_t)i * A + off[i]) : T(0);
-      // the x shift: rotate by one lane; the end lanes take the neighbouring
-      // wavefront's end value (periodic inside the row of nx/64 wavefronts)
-      if (lane == 63) {
-#pragma unroll
-        for (int j = 0; j < 5; ++j) edge[par][0][wv][j] = d[kFromLeft[j]];
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < 5; ++j) edge[par][1][wv][j] = d[kFromRight[j]];
-      }
-      __syncthreads();
-      const int wpr = q.g.nx >> 6;  // wavefronts per row: 1, 2 or 4
-      const int wl = wv & (wpr - 1), rb = wv - wl;
-      const int wleft = rb + ((wl + wpr - 1) & (wpr - 1));
-      const int wright = rb + ((wl + 1) & (wpr - 1));
-#pragma unroll
-      for (int j = 0; j < 5; ++j) {
-        const T l = from_left(d[kFromLeft[j]]);
-        const T r = from_right(d[kFromRight[j]]);
-        d[kFromLeft[j]] = lane == 0 ? edge[par][0][wleft][j] : l;
-        d[kFromRight[j]] = lane == 63 ? edge[par][1][wright][j] : r;
-      }
-      par ^= 1;
+      pull_row<T>(sbase, q.g, act, x, y, z, lane, wv, edge, par, d);
     } else if (act && off32) {
-      // 32-bit offsets inside population i's slab, i A folded into the
-      // scalar base (the replica's 19 S entries fit 32 bits)
-      const uint32_t A = (uint32_t)q.g.A;
-      const int xm = x == 0 ? q.g.nx - 1 : x - 1, xp = x == q.g.nx - 1 ? 0 : x + 1;
-      const int ym = y == 0 ? q.g.ny - 1 : y - 1, yp = y == q.g.ny - 1 ? 0 : y + 1;
-      const int zm = z == 0 ? q.g.nz - 1 : z - 1, zp = z == q.g.nz - 1 ? 0 : z + 1;
-      const uint32_t z0 = (uint32_t)z * 19u * A, zl = (uint32_t)zm * 19u * A,
-                     zh = (uint32_t)zp * 19u * A;
-      const uint32_t r0 = (uint32_t)(y * q.g.nx), rl = (uint32_t)(ym * q.g.nx),
-                     rh = (uint32_t)(yp * q.g.nx);
-      const uint32_t X0 = (uint32_t)x, Xl = (uint32_t)xm, Xh = (uint32_t)xp;
-      // source (plane, row, column) of each population: z - c_z, y - c_y, x - c_x
-      const uint32_t off[19] = {z0 + r0 + X0, z0 + r0 + Xl, z0 + r0 + Xh, z0 + rl + X0,
-                                z0 + rh + X0, zl + r0 + X0, zh + r0 + X0, z0 + rl + Xl,
-                                z0 + rh + Xh, z0 + rh + Xl, z0 + rl + Xh, zl + r0 + Xl,
-                                zh + r0 + Xh, zh + r0 + Xl, zl + r0 + Xh, zl + rl + X0,
-                                zh + rh + X0, zh + rl + X0, zl + rh + X0};
-      // (plain loads: a shifted run straddles cache lines that the
-      // neighbouring wavefront reads too, so the lines should stay in L2)
-#pragma unroll
-      for (int i = 0; i < 19; ++i) d[i] = sbase[(size_t)i * A + off[i]];
+      pull_off32<T>(sbase, q.g, x, y, z, d);
     } else if (act) {
       size_t off[19];
       pull_offsets(q.g, x, y, z, off);
@@ -324,19 +351,20 @@ hipError_t launch_clock_advance(Context* c) {
 }
 
 // ---------------------------------------------------------------------------
-// Block reduction of kRedWidth doubles per thread into out[0..kRedWidth).
+// Block reduction of W <= kRedWidth doubles per thread into out[0..W).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void block_reduce_store(double acc[kRedWidth], double* out) {
-  __shared__ double sh[kBlock / 64][kRedWidth];
+template <int W>
+__device__ __forceinline__ void block_reduce_store(const double acc[W], double* out) {
+  __shared__ double sh[kBlock / 64][W];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-  for (int q = 0; q < kRedWidth; ++q) {
+  for (int q = 0; q < W; ++q) {
     double s = acc[q];
     for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
     if (lane == 0) sh[wv][q] = s;
   }
   __syncthreads();
-  if (threadIdx.x < kRedWidth) {
+  if (threadIdx.x < W) {
     double s = 0.0;
     for (int w = 0; w < kBlock / 64; ++w) s += sh[w][threadIdx.x];
     out[threadIdx.x] = s;
@@ -344,47 +372,83 @@ __device__ __forceinline__ void block_reduce_store(double acc[kRedWidth], double
   __syncthreads();
 }
 
-// Partial sums, one row per item (PerBlock = false) or, for a single
-// replica, one row per block over all its items (PerBlock = true: a bounded
-// number of rows).  Columns: 0 sum drho, 1-3 sum j, 4-6 sum J, 7 sum
-// |j/rho|^2.  Fields (density, velocity) of replica `field_rep`.
-template <typename T, bool PerBlock>
-__global__ __launch_bounds__(kBlock) void k_moments(StreamArgs<T> a, int field_rep,
+// ---------------------------------------------------------------------------
+// Moment sums and fields.  Columns of a partial row: 0 sum drho, 1-3 sum j,
+// 4-6 sum J, 7 sum |j/rho|^2.  Fields (density, velocity) of replica
+// `field_rep`.
+//
+// Bound by the 76 (FP32) bytes a site's populations take, so the pass does
+// little else: populations pulled as in the collide-stream kernel, J read
+// only at marked sites (it is zero elsewhere), and one block reduction per
+// chunk of consecutive items instead of one per 256 sites (a reduction of 16
+// columns costs more than the loads of an item).  A chunk's sums go to one
+// row, numbered by the chunk for a single replica, else by the last item the
+// chunk holds of a replica (chunk_row), since a chunk may span several.
+// 512 replicas of 24-48 sites per edge (29.2 M sites, 2.2 GB): 457 us = 4.9
+// TB/s, against 1000 us with one reduction per item, 64-bit gathers and J
+// read at every site; 50 x 41 x 37: 7.0 against 9.1 us.
+// ---------------------------------------------------------------------------
+constexpr int kMomentCols = 8;
+
+__device__ __forceinline__ int chunk_row(int chunk, int per, int end) {
+  const int e = (chunk + 1) * per;
+  return (e < end ? e : end) - 1;
+}
+
+template <typename T, int Mode>
+__global__ __launch_bounds__(kBlock) void k_moments(StreamArgs<T> a, int per, int field_rep,
                                                     T* __restrict__ rho_out,
                                                     T* __restrict__ u_out,
                                                     double* __restrict__ partials) {
+  __shared__ RowEdges<T> edge;
   const T* __restrict__ src = a.pop[a.clock->cur];
-  double acc[kRedWidth];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int chunk = Mode == 0 ? xcd_first_item() : (int)blockIdx.x;
+  const int end = min((chunk + 1) * per, a.nitems);
+  int par = 0;
+  double acc[kMomentCols];
 #pragma unroll
-  for (int k = 0; k < kRedWidth; ++k) acc[k] = 0.0;
-  for (int item = blockIdx.x; item < a.nitems; item += gridDim.x) {
-    const int rr = a.R == 1 ? 0 : replica_of_item(a.item_off, a.R, item);
-    const RepLB<T>& q = a.rep[rr];
+  for (int k = 0; k < kMomentCols; ++k) acc[k] = 0.0;
+  for (int item = chunk * per; item < end; ++item) {
+    const int rr = __builtin_amdgcn_readfirstlane(
+        a.R == 1 ? 0 : replica_of_item(a.item_off, a.R, item));
+    const RepLB<T> q = scalar_copy(a.rep + rr);
     const int local = (item - q.item_off) * kBlock + threadIdx.x;
-    if (!PerBlock) {
-#pragma unroll
-      for (int k = 0; k < kRedWidth; ++k) acc[k] = 0.0;
-    }
-    if (local < q.g.S) {
-      int x, y, z;
+    const bool act = local < q.g.S;
+    const T* __restrict__ sbase = src + 19 * (size_t)q.site_off;
+    int x, y, z;
+    site_coords(q.g, act ? local : 0, x, y, z);
+    T d[19];
+    const bool rows = Mode == 2 ? q.rows != 0 : Mode == 1;
+    if (rows) {
+      pull_row<T>(sbase, q.g, act, x, y, z, lane, wv, edge, par, d);
+    } else if (act && fits_off32(q.g)) {
+      pull_off32<T>(sbase, q.g, x, y, z, d);
+    } else if (act) {
       size_t off[19];
-      site_coords(q.g, local, x, y, z);
       pull_offsets(q.g, x, y, z, off);
-      const T* __restrict__ sbase = src + 19 * (size_t)q.site_off;
-      T d[19];
 #pragma unroll
       for (int i = 0; i < 19; ++i) d[i] = sbase[off[i]];
+    }
+    if (act) {
       T drho, jx, jy, jz;
       moments_deviation<T>(d, drho, jx, jy, jz);
       const T rho = q.k.rho0 + drho;
-      const Vec4<T> jv = a.J[q.site_off + local];
+      acc[0] += (double)drho;
       acc[1] += (double)jx;
       acc[2] += (double)jy;
       acc[3] += (double)jz;
-      if (a.varc) {
-        jx += jv.x;
-        jy += jv.y;
-        jz += jv.z;
+      const int gsite = q.site_off + local;
+      if ((a.mark[gsite >> 6] >> (gsite & 63)) & 1ull) {
+        const Vec4<T> jv = a.J[gsite];
+        acc[4] += (double)jv.x;
+        acc[5] += (double)jv.y;
+        acc[6] += (double)jv.z;
+        if (a.varc) {
+          jx += jv.x;
+          jy += jv.y;
+          jz += jv.z;
+        }
       }
       if (rr == field_rep) {
         if (rho_out) rho_out[local] = rho;
@@ -395,36 +459,39 @@ __global__ __launch_bounds__(kBlock) void k_moments(StreamArgs<T> a, int field_r
           u_out[2 * S + local] = jz / rho;
         }
       }
-      acc[0] += (double)drho;
-      acc[4] += (double)jv.x;
-      acc[5] += (double)jv.y;
-      acc[6] += (double)jv.z;
-      const double ux = (double)jx / (double)rho, uy = (double)jy / (double)rho,
-                   uz = (double)jz / (double)rho;
+      const double irho = 1.0 / (double)rho;
+      const double ux = (double)jx * irho, uy = (double)jy * irho, uz = (double)jz * irho;
       acc[7] += ux * ux + uy * uy + uz * uz;
     }
-    if (!PerBlock) block_reduce_store(acc, partials + (size_t)item * kRedWidth);
+    // the chunk's last item of this replica: its row
+    const bool last = item + 1 == end || (a.R > 1 && a.item_off[rr + 1] == item + 1);
+    if (last) {
+      block_reduce_store<kMomentCols>(acc, partials + (size_t)(a.R == 1 ? chunk : item) * kRedWidth);
+#pragma unroll
+      for (int k = 0; k < kMomentCols; ++k) acc[k] = 0.0;
+    }
   }
-  if (PerBlock) block_reduce_store(acc, partials + (size_t)blockIdx.x * kRedWidth);
 }
 
-// One block per replica: sum its partial rows (its items' rows, or with
-// nrows > 0, for a single replica, rows [0, nrows)), then its particles'
-// momentum and kinetic energy (columns 8-10 sum v, 11 sum |v|^2).
+// One block per replica: sum its partial rows (for a single replica one per
+// chunk; else those of its chunks), then its particles' momentum and kinetic
+// energy (columns 8-10 sum v, 11 sum |v|^2).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_finalize(StreamArgs<T> a,
                                                      const RepMD* __restrict__ md,
                                                      const double* __restrict__ partials,
                                                      const double* __restrict__ v, int64_t Ntot,
-                                                     double* __restrict__ totals, int nrows) {
+                                                     double* __restrict__ totals, int per) {
   const int rr = blockIdx.x;
-  const int i0 = nrows > 0 ? 0 : a.item_off[rr], i1 = nrows > 0 ? nrows : a.item_off[rr + 1];
-  double acc[kRedWidth];
+  const int i0 = a.item_off[rr], i1 = a.item_off[rr + 1];
+  double acc[12];
 #pragma unroll
-  for (int k = 0; k < kRedWidth; ++k) acc[k] = 0.0;
-  for (int it = i0 + threadIdx.x; it < i1; it += kBlock)
+  for (int k = 0; k < 12; ++k) acc[k] = 0.0;
+  for (int c = i0 / per + threadIdx.x; c <= (i1 - 1) / per; c += kBlock) {
+    const int row = a.R == 1 ? c : chunk_row(c, per, i1);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] += partials[(size_t)it * kRedWidth + k];
+    for (int k = 0; k < kMomentCols; ++k) acc[k] += partials[(size_t)row * kRedWidth + k];
+  }
   if (v) {
     const int p0 = md[rr].part_off, n = md[rr].N;
     for (int p = p0 + threadIdx.x; p < p0 + n; p += kBlock) {
@@ -435,21 +502,42 @@ __global__ __launch_bounds__(kBlock) void k_finalize(StreamArgs<T> a,
       acc[11] += vx * vx + vy * vy + vz * vz;
     }
   }
-  block_reduce_store(acc, totals + (size_t)rr * kRedWidth);
+  block_reduce_store<12>(acc, totals + (size_t)rr * kRedWidth);
+}
+
+// Items per chunk: one reduction per 4 items once there are enough chunks to
+// fill the chip several times over; at most max_rows chunks.
+static int moment_chunk(int nitems, int max_rows) {
+  const int per = std::min(4, std::max(1, nitems / 4096));
+  return std::max(per, (nitems + max_rows - 1) / max_rows);
+}
+
+template <typename T>
+static hipError_t moments_launch(Context* c, const StreamArgs<T>& a, int per, int rep, void* d_rho,
+                                 void* d_u, double* partials) {
+  const dim3 grid((unsigned)((a.nitems + per - 1) / per));
+  if (c->plan.row_replicas == c->plan.R)
+    hipLaunchKernelGGL((k_moments<T, 1>), grid, dim3(kBlock), 0, c->stream, a, per, rep,
+                       (T*)d_rho, (T*)d_u, partials);
+  else if (c->plan.row_replicas == 0)
+    hipLaunchKernelGGL((k_moments<T, 0>), grid, dim3(kBlock), 0, c->stream, a, per, rep,
+                       (T*)d_rho, (T*)d_u, partials);
+  else
+    hipLaunchKernelGGL((k_moments<T, 2>), grid, dim3(kBlock), 0, c->stream, a, per, rep,
+                       (T*)d_rho, (T*)d_u, partials);
+  return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t moments_t(Context* c, int rep, void* d_rho, void* d_u, double* d_totals) {
   StreamArgs<T> a = stream_args<T>(c);
   double* partials = (double*)at(c, c->plan.lay.partials);
-  const int blocks = c->tune.lb_blocks > 0 ? std::min(c->tune.lb_blocks, a.nitems) : a.nitems;
-  hipLaunchKernelGGL((k_moments<T, false>), dim3(blocks), dim3(kBlock), 0, c->stream, a, rep,
-                     (T*)d_rho, (T*)d_u, partials);
-  hipError_t e = hipGetLastError();
+  const int per = moment_chunk(a.nitems, a.nitems);
+  const hipError_t e = moments_launch<T>(c, a, per, rep, d_rho, d_u, partials);
   if (e != hipSuccess || !d_totals) return e;
   hipLaunchKernelGGL(k_finalize<T>, dim3(c->plan.R), dim3(kBlock), 0, c->stream, a,
                      (const RepMD*)at(c, c->plan.lay.rep_md), partials,
-                     (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot, d_totals, 0);
+                     (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot, d_totals, per);
   return hipGetLastError();
 }
 
@@ -461,8 +549,8 @@ hipError_t launch_moments(Context* c, int rep, void* d_rho, void* d_u, double* d
 // ---------------------------------------------------------------------------
 // Moments without workspace scratch (lb_moments_noalloc): the reduction rows
 // live in a fixed device array of this library instead of the context's
-// workspace.  At most kScratchRows blocks, each summing the items it strides
-// over into one row, then the totals row.  Every call overwrites all the
+// workspace.  At most kScratchRows chunks, each summed into one row, then
+// the totals row.  Every call overwrites all the
 // rows it reads, so nothing needs clearing; calls that overlap on one GPU
 // (two streams) race on the array.
 // ---------------------------------------------------------------------------
@@ -495,15 +583,13 @@ hipError_t moments_scratch(double** out) {
 template <typename T>
 static hipError_t moments_rows_t(Context* c, void* d_rho, void* d_u, double* rows) {
   StreamArgs<T> a = stream_args<T>(c);
-  const int blocks = std::min(kScratchRows, a.nitems);
-  hipLaunchKernelGGL((k_moments<T, true>), dim3(blocks), dim3(kBlock), 0, c->stream, a, 0,
-                     (T*)d_rho, (T*)d_u, rows);
-  hipError_t e = hipGetLastError();
+  const int per = moment_chunk(a.nitems, kScratchRows);
+  const hipError_t e = moments_launch<T>(c, a, per, 0, d_rho, d_u, rows);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_finalize<T>, dim3(1), dim3(kBlock), 0, c->stream, a,
                      (const RepMD*)at(c, c->plan.lay.rep_md), rows,
                      (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot,
-                     rows + (size_t)kScratchRows * kRedWidth, blocks);
+                     rows + (size_t)kScratchRows * kRedWidth, per);
   return hipGetLastError();
 }
 
@@ -516,45 +602,71 @@ hipError_t launch_moments_rows(Context* c, void* d_rho, void* d_u, double* rows)
 // Copies between pull storage and the plain post-stream layout of one
 // replica ([19][S] and [3][S] arrays in the run precision).
 // ---------------------------------------------------------------------------
+// Copy out: the populations pulled as in the collide-stream kernel (aligned
+// rows or 32-bit offsets) and stored past the caches, one 256-site item per
+// block.  Bound by memory, with the 19 separate output arrays as its limit:
+// 435 us at 256^3 in FP32 (5.9 TB/s; the collide-stream kernel, which writes
+// interleaved planes, 6.3), against 449 us with 64-bit gathers and cached
+// stores.
 // Variant 3 (pend != nullptr): a copy out adds the increments of the
 // transfer the site has received in the current interval (J at marked
 // sites), so that it shows the populations as the paper's variant C holds
 // them after each MD step.
+template <typename T, int Mode>
+__global__ __launch_bounds__(kBlock) void k_get_pop(const T* __restrict__ pop,
+                                                    T* __restrict__ plain,
+                                                    const Vec4<T>* __restrict__ pend,
+                                                    const unsigned long long* __restrict__ mark,
+                                                    const RepLB<T>* __restrict__ rep, int rr) {
+  __shared__ RowEdges<T> edge;
+  const RepLB<T> q = scalar_copy(rep + rr);
+  const int item = Mode == 0 ? xcd_first_item() : (int)blockIdx.x;
+  const int r = item * kBlock + threadIdx.x;
+  const bool act = r < q.g.S;
+  const T* __restrict__ sbase = pop + 19 * (size_t)q.site_off;
+  int x, y, z, par = 0;
+  site_coords(q.g, act ? r : 0, x, y, z);
+  T d[19];
+  if (Mode == 1)
+    pull_row<T>(sbase, q.g, act, x, y, z, threadIdx.x & 63, threadIdx.x >> 6, edge, par, d);
+  if (!act) return;
+  if (Mode == 0) {
+    if (fits_off32(q.g)) {
+      pull_off32<T>(sbase, q.g, x, y, z, d);
+    } else {
+      size_t off[19];
+      pull_offsets(q.g, x, y, z, off);
+#pragma unroll
+      for (int i = 0; i < 19; ++i) d[i] = sbase[off[i]];
+    }
+  }
+  const int gs = q.site_off + r;
+  if (pend && ((mark[gs >> 6] >> (gs & 63)) & 1ull)) {
+    const Vec4<T> jv = pend[gs];
+    T drho, jx, jy, jz, sm[6], dd[19];
+    moments_deviation<T>(d, drho, jx, jy, jz);
+    varc_stress<T>(jx, jy, jz, T(1) / (q.k.rho0 + drho), jv.x, jv.y, jv.z, q.k.hb, q.k.hs, sm);
+    mode_increments_to_pops<T>(jv.x, jv.y, jv.z, sm, dd);
+#pragma unroll
+    for (int i = 0; i < 19; ++i) d[i] += dd[i];
+  }
+  const size_t S = (size_t)q.g.S;
+#pragma unroll
+  for (int i = 0; i < 19; ++i) __builtin_nontemporal_store(d[i], plain + (size_t)i * S + r);
+}
+
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_copy_pop(T* __restrict__ pop, int site_off,
-                                                     Geom g, T* __restrict__ plain, int to_plain,
-                                                     const Vec4<T>* __restrict__ pend,
-                                                     const unsigned long long* __restrict__ mark,
-                                                     const RepLB<T>* __restrict__ rep, int rr) {
+__global__ __launch_bounds__(kBlock) void k_set_pop(T* __restrict__ pop, int site_off, Geom g,
+                                                    const T* __restrict__ plain) {
   const int r = blockIdx.x * kBlock + threadIdx.x;
   if (r >= g.S) return;
   int x, y, z;
   size_t off[19];
   site_coords(g, r, x, y, z);
   pull_offsets(g, x, y, z, off);
-  const size_t S = (size_t)g.S;
   T* __restrict__ base = pop + 19 * (size_t)site_off;
-  if (!to_plain) {
 #pragma unroll
-    for (int i = 0; i < 19; ++i) base[off[i]] = plain[(size_t)i * S + r];
-    return;
-  }
-  T d[19];
-#pragma unroll
-  for (int i = 0; i < 19; ++i) d[i] = base[off[i]];
-  const int gs = site_off + r;
-  if (pend && ((mark[gs >> 6] >> (gs & 63)) & 1ull)) {
-    const Vec4<T> jv = pend[gs];
-    const CollideConsts<T>& k = rep[rr].k;
-    T drho, jx, jy, jz, sm[6], dd[19];
-    moments_deviation<T>(d, drho, jx, jy, jz);
-    varc_stress<T>(jx, jy, jz, T(1) / (k.rho0 + drho), jv.x, jv.y, jv.z, k.hb, k.hs, sm);
-    mode_increments_to_pops<T>(jv.x, jv.y, jv.z, sm, dd);
-#pragma unroll
-    for (int i = 0; i < 19; ++i) d[i] += dd[i];
-  }
-#pragma unroll
-  for (int i = 0; i < 19; ++i) plain[(size_t)i * S + r] = d[i];
+  for (int i = 0; i < 19; ++i) base[off[i]] = plain[(size_t)i * g.S + r];
 }
 
 template <typename T>
@@ -587,12 +699,20 @@ static hipError_t copy_t(Context* c, int rep, void* plain, int what) {
     return hipGetLastError();
   }
   T* pop = (T*)c->popv[c->cur];
-  const bool pend = c->p[0].variant == 3;
-  hipLaunchKernelGGL(k_copy_pop<T>, dim3(blocks), dim3(kBlock), 0, c->stream, pop,
-                     site_off, g, (T*)plain, what == 0 ? 1 : 0,
-                     pend ? (const Vec4<T>*)at(c, c->plan.lay.transfer) : nullptr,
-                     (const unsigned long long*)at(c, c->plan.lay.mark),
-                     (const RepLB<T>*)at(c, c->plan.lay.rep_lb), rep);
+  if (what == 1) {
+    hipLaunchKernelGGL(k_set_pop<T>, dim3(blocks), dim3(kBlock), 0, c->stream, pop, site_off, g,
+                       (const T*)plain);
+    return hipGetLastError();
+  }
+  const Vec4<T>* pend = p.variant == 3 ? (const Vec4<T>*)at(c, c->plan.lay.transfer) : nullptr;
+  const unsigned long long* mark = (const unsigned long long*)at(c, c->plan.lay.mark);
+  const RepLB<T>* tab = (const RepLB<T>*)at(c, c->plan.lay.rep_lb);
+  if (row_path(p))
+    hipLaunchKernelGGL((k_get_pop<T, 1>), dim3(blocks), dim3(kBlock), 0, c->stream, pop, (T*)plain,
+                       pend, mark, tab, rep);
+  else
+    hipLaunchKernelGGL((k_get_pop<T, 0>), dim3(blocks), dim3(kBlock), 0, c->stream, pop, (T*)plain,
+                       pend, mark, tab, rep);
   return hipGetLastError();
 }
 
