@@ -221,11 +221,16 @@ RepMD rep_md(const Context* c, int r) {
   m.L[0] = p.nx;
   m.L[1] = p.ny;
   m.L[2] = p.nz;
+  for (int d = 0; d < 3; ++d) m.inv_L[d] = 1.0 / m.L[d];
   for (int d = 0; d < 3; ++d) m.f_ext[d] = p.f_ext[d];
   m.k_bond = p.k_bond;
   m.r0_bond = p.r0_bond;
-  m.wca_eps = p.wca_eps;
-  m.wca_sigma = p.wca_sigma;
+  // pair cut-off squared: (2^(1/6) sigma)^2 (WCA) or (2^(7/6) sigma)^2
+  m.pair_sig2 = p.wca_sigma * p.wca_sigma;
+  m.pair_rc2 = (p.force_model == 2 ? 1.2599210498948732 : 5.0396841995794928) * p.wca_sigma *
+               p.wca_sigma;
+  m.pair_eps24 = 24.0 * p.wca_eps;
+  m.inv_chain = 1.0 / m.chain_len;
   const int Ls[3] = {p.nx, p.ny, p.nz};
   for (int d = 0; d < 3; ++d) {
     const int n = cells_per_axis(&p, d);

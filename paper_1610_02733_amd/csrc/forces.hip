@@ -57,31 +57,62 @@ __global__ __launch_bounds__(kBlock) void k_bin_count(const double* __restrict__
 // rounding), with minimum-image separations.  Force models 0 and 1 give zero
 // or the constant f_ext.
 //
-// 32 lanes per particle: lanes 0-26 scan the slots of one neighbouring cell
-// each (offsets -1, 0, +1 per axis; on an axis with fewer than 3 cells,
-// cells 0, 1, 2 of that axis instead, so every distinct cell is scanned
-// once), lane 27 adds the two chain bonds, lane 28 scans the overflow list
-// (empty unless a cell holds more than cell_cap particles; a pair closer
-// than the cut-off lies in neighbouring cells, so the list's particles need
-// only the distance test); the lane sums are a butterfly reduction.  The
-// half of the counts comes with the particle's own count entry.  Lane 0
-// stores the force and, after an MD step, applies the second half-kick of
-// velocity Verlet (new conservative force + the coupling force held over the
-// step).  After an MD step the launch also carries the step's after-step
-// work in extra blocks: this kernel runs after every particle of the step
-// has read the transfer field.
+// 32 lanes per particle.  Lanes 0-26 take one neighbouring cell each (offsets
+// -1, 0, +1 per axis; on an axis with fewer than 3 cells, cells 0, 1, 2 of
+// that axis instead, so every distinct cell is taken once) and put its
+// particles into the particle's list in LDS, at the place a prefix sum of the
+// cell counts gives; then all 32 lanes share the list evenly.  (One lane per
+// cell throughout ran as long as its fullest cell, about twice the even
+// share, with the cut-off test and force of two slots per cell evaluated
+// whether filled or not.)  Lanes 27 and 28 add the bond to the chain's
+// previous and next bead, lane 29 scans the overflow list (empty unless a
+// cell holds more than cell_cap particles; a pair closer than the cut-off
+// lies in neighbouring cells, so the list's particles need only the distance
+// test); the lane sums are a butterfly reduction.  The half of the counts
+// comes with the particle's own count entry.  Lanes 0-2 store the force and,
+// after an MD step, apply the second half-kick of velocity Verlet (new
+// conservative force + the coupling force held over the step).  After an MD
+// step the launch also carries the step's after-step work in extra blocks:
+// this kernel runs after every particle of the step has read the transfer
+// field.
+//
+// Dense systems are bound by FP64 issue, dilute ones by the chain of three
+// dependent loads (cell entry and position, counts and slots, positions).
+// The pair arithmetic therefore has no division but one reciprocal: minimum
+// images by 1/L, 1/r^2 by two Newton steps on the hardware's estimate.
+// Measured with the five divisions and one lane per cell it had before: 13.8,
+// 19.0 and 29.4 us per MD step for 128^3 WCA chains, Kremer-Grest chains and
+// 5 x 2560 Kremer-Grest beads at 0.32 per site; now 9.5, 10.2 and 16.5 us.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double min_image(double d, double L) { return d - L * rint(d / L); }
+__device__ __forceinline__ double min_image(double d, double L, double inv_L) {
+  return d - L * rint(d * inv_L);
+}
+
+// 1/a for finite normal a > 0: two Newton steps square the estimate's error
+// twice, to the last bit or two.
+__device__ __forceinline__ double reciprocal(double a) {
+  double y = __builtin_amdgcn_rcp(a);
+  y = fma(y, fma(-a, y, 1.0), y);
+  return fma(y, fma(-a, y, 1.0), y);
+}
 
 constexpr int kForceLanes = 32;
 
+// Sum over the 32 lanes of a particle, on every lane: inside a row of 16 by
+// DPP (lanes 1 and 2 apart by quad permutations, then the mirrored half row
+// and row, which hold the other groups' sums), the two rows by a shuffle.
+template <int Ctrl>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), Ctrl, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), Ctrl, 0xF, 0xF, false);
+  return v + __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double lane32_sum(double v) {
-  v += __shfl_xor(v, 16, kForceLanes);
-  v += __shfl_xor(v, 8, kForceLanes);
-  v += __shfl_xor(v, 4, kForceLanes);
-  v += __shfl_xor(v, 2, kForceLanes);
-  v += __shfl_xor(v, 1, kForceLanes);
-  return v;
+  v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  v = dpp_add<0x140>(v);  // row_mirror
+  return v + __shfl_xor(v, 16, kForceLanes);
 }
 
 template <typename T>
@@ -102,35 +133,172 @@ struct ForceArgs {
 };
 
 // Pair force of the WCA or cut Lennard-Jones potential on the particle at X
-// from particle q, added to F when q lies within the cut-off.
-__device__ __forceinline__ void add_pair_force(const double* __restrict__ x, int64_t N,
-                                               const double X[3], int q, const RepMD& m,
-                                               double rc2, double sig2, double F[3]) {
+// from one at Y, added to F when `use` and Y lies within the cut-off.
+__device__ __forceinline__ void add_pair_force(const double X[3], const double Y[3], bool use,
+                                               const RepMD& m, double F[3]) {
   double dx[3], r2 = 0.0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    dx[d] = min_image(X[d] - x[d * N + q], m.L[d]);
+    dx[d] = min_image(X[d] - Y[d], m.L[d], m.inv_L[d]);
     r2 += dx[d] * dx[d];
   }
-  if (r2 >= rc2) return;
-  const double sr2 = sig2 / r2;
+  if (!use || !(r2 < m.pair_rc2)) return;
+  const double ir2 = r2 > 0.0 ? reciprocal(r2) : __builtin_inf();
+  const double sr2 = m.pair_sig2 * ir2;
   const double sr6 = sr2 * sr2 * sr2;
-  const double fm = 24.0 * m.wca_eps * (2.0 * sr6 * sr6 - sr6) / r2;
+  const double fm = m.pair_eps24 * (2.0 * sr6 * sr6 - sr6) * ir2;
 #pragma unroll
   for (int d = 0; d < 3; ++d) F[d] += fm * dx[d];
+}
+
+// Candidates of one particle at a time in LDS (a longer list is taken in
+// windows): 8 KB a block, which leaves the waves per CU to the registers.
+constexpr int kPairList = 256;
+
+// Forces of the particle the 32 lanes share: replica constants m, its slot p.
+template <typename T, bool Kick>
+__device__ __forceinline__ void force_particle(const ForceArgs<T>& a, const RepMD& m, int64_t p,
+                                               int lane, int32_t* __restrict__ list) {
+  const int64_t N = a.N;
+  double F[3] = {0.0, 0.0, 0.0};
+  // (the cells are written for every particle when a replica has them)
+  const bool pairs = m.force_model >= 2;
+  const int g = pairs ? a.bin[p] : -1;
+  const double X[3] = {a.x[p], a.x[N + p], a.x[2 * N + p]};
+  // lanes 0-2 finish the particle, one component each
+  const bool kick = Kick && lane < 3 && m.split_kick;
+  double vv = 0.0, fh = 0.0;
+  if (kick) {
+    vv = a.v[lane * N + p];
+    fh = a.fc_held[lane * N + p];
+  }
+  // the bond partner of lanes 27 and 28
+  bool bond = false;
+  int64_t qb = p;
+  if (pairs && (lane == 27 || lane == 28)) {
+    int pos;
+    div_fast((int)(p - m.part_off), m.chain_len, m.inv_chain, pos);
+    bond = lane == 27 ? pos > 0 : pos < m.chain_len - 1;
+    if (bond) qb = lane == 27 ? p - 1 : p + 1;
+  }
+  const double B[3] = {a.x[qb], a.x[N + qb], a.x[2 * N + qb]};
+  if (g >= 0) {
+    const int half = g >= a.ncells ? 1 : 0;
+    // this lane's cell: its count and first eight slots at once (cap >= 8; a
+    // slot past the count holds a stale index and is not used)
+    int n = 0;
+    const int32_t* __restrict__ sl = a.slot;
+    int4 s0 = make_int4(0, 0, 0, 0), s1 = s0;
+    {
+      const int o[3] = {lane % 3, (lane / 3) % 3, lane / 9};
+      int cc[3], q3[3];
+      local_cell_coords(X, m, cc);
+      bool use = lane < 27;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (m.nb[d] < 3) {
+          q3[d] = o[d];
+          use = use && o[d] < m.nb[d];
+        } else {
+          const int qq = cc[d] + o[d] - 1;
+          q3[d] = qq < 0 ? qq + m.nb[d] : (qq >= m.nb[d] ? qq - m.nb[d] : qq);
+        }
+      }
+      if (use) {
+        const int cell = m.cell_off + q3[0] + m.nb[0] * (q3[1] + m.nb[1] * q3[2]);
+        sl += (int64_t)cell * a.cap;
+        n = min(a.count[half * a.ncells + cell], a.cap);
+        s0 = reinterpret_cast<const int4*>(sl)[0];
+        s1 = reinterpret_cast<const int4*>(sl)[1];
+      }
+    }
+    const int no = lane == 29 ? a.count[2 * a.ncells + half] : 0;
+    if (bond) {
+      // (while the counts and slots are on their way) harmonic (model 2) or
+      // FENE (model 3, no finite force at r >= R0)
+      double dx[3], r2 = 0.0;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        dx[d] = min_image(X[d] - B[d], m.L[d], m.inv_L[d]);
+        r2 += dx[d] * dx[d];
+      }
+      double fm;
+      if (m.force_model == 2) {
+        const double r = sqrt(r2);
+        fm = -m.k_bond * (r - m.r0_bond) / r;
+      } else {
+        const double x2 = r2 / (m.r0_bond * m.r0_bond);
+        fm = x2 < 1.0 ? -m.k_bond / (1.0 - x2) : __builtin_nan("");
+      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) F[d] += fm * dx[d];
+    }
+    // place of the cell's particles in the list, and the list's length: the
+    // sum over the lanes up to this one, inside a row of 16 by DPP shifts,
+    // the lower row's total into the upper one by a row broadcast
+    int pre = n;
+    pre += __builtin_amdgcn_update_dpp(0, pre, 0x111, 0xF, 0xF, true);
+    pre += __builtin_amdgcn_update_dpp(0, pre, 0x112, 0xF, 0xF, true);
+    pre += __builtin_amdgcn_update_dpp(0, pre, 0x114, 0xF, 0xF, true);
+    pre += __builtin_amdgcn_update_dpp(0, pre, 0x118, 0xF, 0xF, true);
+    pre += __builtin_amdgcn_update_dpp(0, pre, 0x142, 0xA, 0xF, false);
+    const int total = __shfl(pre, kForceLanes - 1, kForceLanes);
+    pre -= n;
+    for (int w = 0; w < total; w += kPairList) {
+      const int at = pre - w;
+      const int s8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (j < n && (unsigned)(at + j) < (unsigned)kPairList) list[at + j] = s8[j];
+      for (int j = 8; j < n; ++j)
+        if ((unsigned)(at + j) < (unsigned)kPairList) list[at + j] = sl[j];
+      // the 32 lanes belong to one wavefront, whose LDS accesses are in order
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int len = min(total - w, kPairList);
+      for (int i = lane; i < len; i += kForceLanes) {
+        const int q = list[i];
+        const double Y[3] = {a.x[q], a.x[N + q], a.x[2 * N + q]};
+        add_pair_force(X, Y, q != p, m, F);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if (no > 0) {
+      const int rep = a.part_rep[p];
+      for (int e = 0; e < no; ++e) {
+        const int q = a.ovf[e];
+        const double Y[3] = {a.x[q], a.x[N + q], a.x[2 * N + q]};
+        add_pair_force(X, Y, q != p && a.part_rep[q] == rep, m, F);
+      }
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) F[d] = lane32_sum(F[d]);
+  if (m.force_model == 1) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) F[d] = m.f_ext[d];
+  }
+  if (lane < 3) {
+    const double f = lane == 0 ? F[0] : (lane == 1 ? F[1] : F[2]);
+    a.f[lane * N + p] = f;
+    if (kick && isfinite(vv)) a.v[lane * N + p] = vv + m.h * (f + fh);
+  }
 }
 
 // Blocks [0, nfb) compute the forces; with AfterST >= 0 (after an MD step,
 // not recording) blocks [nfb, nfb + 2 nseg) do the after-step work
 // of the MD step just taken (after_step_item), which is independent of the
 // forces: it touches J, the claims and the corner cache only.
-// One (a single replica): its constants are read once, before the loop
-// (uniform, scalar loads), so the particle's loads need not wait for them.
-// The loads of a particle are issued together where they do not depend on
-// each other: its cell, position and (lane 0) velocity and held coupling
-// force; a cell's count with its first two slots; the two bond partners.
+// The replica's constants are in scalar registers: read once with a single
+// replica (One); otherwise per wavefront, whose two particles nearly always
+// belong to one replica (and are taken one after the other where they do
+// not).
+// Held to 7 waves per SIMD: the latency of a particle's loads is hidden by the
+// other waves, and 1e4 particles with their after-step blocks then run in one
+// round (5 waves as the registers would have it: 883 against 821 us for three
+// cycles of the 128^3 polymer, 1549 against 1430 us for five of 5 x 2560
+// dense beads; 6: 821 and 1520; 8, with spills: 843 and 1515).
 template <typename T, bool Kick, int AfterST, bool One>
-__global__ __launch_bounds__(kBlock) void k_forces(ForceArgs<T> a, CoupleArgs<T> ca, int64_t nseg,
+__global__ __launch_bounds__(kBlock, 7) void k_forces(ForceArgs<T> a, CoupleArgs<T> ca, int64_t nseg,
                                                    int per, int L, int64_t nfb) {
   if constexpr (AfterST >= 0) {
     if (blockIdx.x >= nfb) {
@@ -138,120 +306,30 @@ __global__ __launch_bounds__(kBlock) void k_forces(ForceArgs<T> a, CoupleArgs<T>
       return;
     }
   }
+  __shared__ int32_t lists[kBlock / kForceLanes][kPairList];
   const int64_t N = a.N;
   RepMD m1;
-  if constexpr (One) m1 = a.md[0];
+  if constexpr (One) m1 = scalar_copy(a.md);
+  const int lane = threadIdx.x & (kForceLanes - 1);
+  int32_t* list = lists[threadIdx.x / kForceLanes];
   // lanes come in whole particles (32 | kBlock), as the shuffles require
   for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < N * kForceLanes;
        t += nfb * kBlock) {
     const int64_t p = t / kForceLanes;
-    const int lane = (int)(t & (kForceLanes - 1));
-    RepMD mr;
-    if constexpr (!One) mr = a.md[a.part_rep[p]];
-    const RepMD& m = One ? m1 : mr;
-    double F[3] = {0.0, 0.0, 0.0};
-    // (the cells are written for every particle when a replica has them)
-    const int g = m.force_model >= 2 ? a.bin[p] : -1;
-    const double X[3] = {a.x[p], a.x[N + p], a.x[2 * N + p]};
-    const bool kick = Kick && lane == 0 && m.split_kick;
-    double vv[3] = {0.0, 0.0, 0.0}, fh[3] = {0.0, 0.0, 0.0};
-    if (kick) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        vv[d] = a.v[d * N + p];
-        fh[d] = a.fc_held[d * N + p];
-      }
-    }
-    if (g >= 0) {
-      const int half = g >= a.ncells ? 1 : 0;
-      const int c = g - (half ? (int)a.ncells : 0);
-      const int32_t* __restrict__ cnt = a.count + half * a.ncells;
-      // pair cut-off squared: (2^(1/6) sigma)^2 (WCA) or (2^(7/6) sigma)^2
-      const double rc2 = (m.force_model == 2 ? 1.2599210498948732 : 5.0396841995794928) *
-                         m.wca_sigma * m.wca_sigma;
-      const double sig2 = m.wca_sigma * m.wca_sigma;
-      if (lane < 27) {
-        const int o[3] = {lane % 3, (lane / 3) % 3, lane / 9};
-        const int lc = c - m.cell_off;
-        const int cc[3] = {lc % m.nb[0], (lc / m.nb[0]) % m.nb[1], lc / (m.nb[0] * m.nb[1])};
-        int q3[3];
-        bool use = true;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          if (m.nb[d] < 3) {
-            q3[d] = o[d];
-            use = use && o[d] < m.nb[d];
-          } else {
-            const int qq = cc[d] + o[d] - 1;
-            q3[d] = qq < 0 ? qq + m.nb[d] : (qq >= m.nb[d] ? qq - m.nb[d] : qq);
-          }
+    if constexpr (One) {
+      force_particle<T, Kick>(a, m1, p, lane, list);
+    } else {
+      const int rep = a.part_rep[p];
+      // (a loop on the wavefront's own mask, so that the body stays inside it)
+      for (unsigned long long todo = __ballot(1); todo != 0;) {
+        const bool mine = rep == __builtin_amdgcn_readlane(rep, __ffsll(todo) - 1);
+        if (mine) {
+          // (read again from the lanes taken: the compiler would put `rep`, a
+          // vector register, in place of a value known to equal it)
+          const RepMD mr = scalar_copy(a.md + __builtin_amdgcn_readfirstlane(rep));
+          force_particle<T, Kick>(a, mr, p, lane, list);
         }
-        if (use) {
-          const int cell = m.cell_off + q3[0] + m.nb[0] * (q3[1] + m.nb[1] * q3[2]);
-          const int32_t* __restrict__ sl = a.slot + (int64_t)cell * a.cap;
-          // the count and the first two slots at once (cap >= 2; a slot past
-          // the count holds a stale index, replaced by p and not used)
-          const int n = min(cnt[cell], a.cap);
-          const int s0 = sl[0], s1 = sl[1];
-          const int q0 = n > 0 ? s0 : (int)p, q1 = n > 1 ? s1 : (int)p;
-          double F0[3] = {0.0, 0.0, 0.0}, F1[3] = {0.0, 0.0, 0.0};
-          add_pair_force(a.x, N, X, q0, m, rc2, sig2, F0);
-          add_pair_force(a.x, N, X, q1, m, rc2, sig2, F1);
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            if (q0 != p) F[d] += F0[d];
-            if (q1 != p) F[d] += F1[d];
-          }
-          for (int s = 2; s < n; ++s) {
-            const int q = sl[s];
-            if (q != p) add_pair_force(a.x, N, X, q, m, rc2, sig2, F);
-          }
-        }
-      } else if (lane == 27) {
-        // bonds to the chain neighbours: harmonic (model 2) or FENE (model 3,
-        // no finite force at r >= R0); both partners' positions at once
-        const int pos = (int)((p - m.part_off) % m.chain_len);
-        const bool has[2] = {pos > 0, pos < m.chain_len - 1};
-        const int64_t qs[2] = {has[0] ? p - 1 : p, has[1] ? p + 1 : p};
-        double dx[2][3], r2[2] = {0.0, 0.0};
-#pragma unroll
-        for (int side = 0; side < 2; ++side)
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            dx[side][d] = min_image(X[d] - a.x[d * N + qs[side]], m.L[d]);
-            r2[side] += dx[side][d] * dx[side][d];
-          }
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-          if (!has[side]) continue;
-          double fm;
-          if (m.force_model == 2) {
-            const double r = sqrt(r2[side]);
-            fm = -m.k_bond * (r - m.r0_bond) / r;
-          } else {
-            const double x2 = r2[side] / (m.r0_bond * m.r0_bond);
-            fm = x2 < 1.0 ? -m.k_bond / (1.0 - x2) : __builtin_nan("");
-          }
-#pragma unroll
-          for (int d = 0; d < 3; ++d) F[d] += fm * dx[side][d];
-        }
-      } else if (lane == 28) {
-        const int no = a.count[2 * a.ncells + half];
-        const int rep = a.part_rep[p];
-        for (int e = 0; e < no; ++e) {
-          const int q = a.ovf[e];
-          if (q != p && a.part_rep[q] == rep) add_pair_force(a.x, N, X, q, m, rc2, sig2, F);
-        }
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) F[d] = lane32_sum(F[d]);
-    if (lane == 0) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        if (m.force_model == 1) F[d] = m.f_ext[d];
-        a.f[d * N + p] = F[d];
-        if (kick && isfinite(vv[d])) a.v[d * N + p] = vv[d] + m.h * (F[d] + fh[d]);
+        todo &= ~__ballot(mine);
       }
     }
   }

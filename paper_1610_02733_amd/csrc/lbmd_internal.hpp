@@ -54,8 +54,11 @@ struct RepMD {
                                     // amplitude before the balance factor (noise_amplitude)
   double inv_m;                     // 1 / particle mass (0 without particles)
   double L[3];
+  double inv_L[3];
   double f_ext[3];
-  double k_bond, r0_bond, wca_eps, wca_sigma;
+  double k_bond, r0_bond;
+  double pair_rc2, pair_sig2, pair_eps24;  // pair cut-off squared, sigma^2, 24 eps
+  double inv_chain;                        // 1 / chain_len
   int nb[3];  // force-cell grid
   double inv_edge[3];
 };

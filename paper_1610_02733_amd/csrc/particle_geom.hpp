@@ -34,14 +34,17 @@ __device__ __forceinline__ int cell_of(int c, int n) {
 }
 
 // Force cell of a position on its replica's cell grid (clamped to the grid).
-__device__ __forceinline__ int local_cell(const double X[3], const RepMD& m) {
-  int c[3];
+__device__ __forceinline__ void local_cell_coords(const double X[3], const RepMD& m, int c[3]) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     int q = (int)floor(X[d] * m.inv_edge[d]);
     q = q < 0 ? 0 : (q >= m.nb[d] ? m.nb[d] - 1 : q);
     c[d] = q;
   }
+}
+__device__ __forceinline__ int local_cell(const double X[3], const RepMD& m) {
+  int c[3];
+  local_cell_coords(X, m, c);
   return c[0] + m.nb[0] * (c[1] + m.nb[1] * c[2]);
 }
 
