@@ -217,7 +217,8 @@ RepMD rep_md(const Context* c, int r) {
   m.amp = sqrt(2.0 * p.friction * p.kT / tau);
   m.tau = tau;
   m.h = p.n_particles > 0 ? tau / (2.0 * p.particle_mass) : 0.0;
-  m.inv_m = p.n_particles > 0 ? 1.0 / p.particle_mass : 0.0;
+  m.bal0 = 1.0 - 0.5 * p.friction * tau * (p.n_particles > 0 ? 1.0 / p.particle_mass : 0.0);
+  m.bal1 = 0.5 * p.friction * tau / p.rho0;
   m.L[0] = p.nx;
   m.L[1] = p.ny;
   m.L[2] = p.nz;
@@ -374,6 +375,13 @@ hipError_t substep_launches(Context* c, int substep) {
   return e;
 }
 
+// The n MD steps of an LB interval from its start.
+hipError_t interval_launches(Context* c, int n) {
+  hipError_t e = hipSuccess;
+  for (int s = 0; s < n && e == hipSuccess; ++s) e = substep_launches(c, s);
+  return e;
+}
+
 }  // namespace
 
 extern "C" {
@@ -482,7 +490,7 @@ int lbmd_run_cycles(lbmd* c, int32_t ncycles) {
     c->stream = c->capture_stream;
     hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
     const int32_t saved_subs = c->subs;
-    for (int s = 0; s < n && e == hipSuccess; ++s) e = substep_launches(c, s);
+    if (e == hipSuccess) e = interval_launches(c, n);
     c->subs = n;  // MD steps the clock advance accounts for
     if (e == hipSuccess) e = launch_collide_stream(c);
     if (e == hipSuccess) e = launch_clock_advance(c);
@@ -871,7 +879,7 @@ int lbmd_adjoint_record(lbmd* c, const void* d_state, int32_t ncycles) {
     a.src[j] = src;
     a.t_lb[j] = c->t_lb;
     a.t_md[j] = c->t_md;
-    for (int s = 0; s < n && e == hipSuccess; ++s) e = substep_launches(c, s);
+    e = interval_launches(c, n);
     c->subs = n;
     if (e == hipSuccess) e = launch_collide_stream(c);
     if (e == hipSuccess) e = launch_clock_advance(c);

@@ -49,6 +49,70 @@ __device__ __forceinline__ T quad_sum(T v) {  // over the 4 lanes of a corner
   return v;
 }
 
+// One of the 32 lanes of particle p (32 | block size: a particle's lanes stay
+// together).
+template <bool Local, typename T>
+__device__ __forceinline__ void refill_particle(const CoupleArgs<T>& a, const RepMD& m,
+                                                const T* __restrict__ pop, int64_t p) {
+  const int sl = threadIdx.x & (kRefillLanes - 1);
+  const int k = sl >> 2, c = sl & 3;
+  const int64_t N = a.N;
+  double X[3];
+  bool finite = true;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    X[d] = a.x[d * N + p];
+    finite = finite && isfinite(X[d]);
+  }
+  if (!finite) return;
+  Cube q;
+  cube_of(X, m.g, q);
+  int cx, cy, cz, site;
+  double w;
+  corner_of(q, m.g, k, cx, cy, cz, site, w);
+  T drho = T(0), qx = T(0), qy = T(0), qz = T(0);
+#pragma unroll
+  for (int mm = 0; mm < 5; ++mm) {
+    const int i = c + 4 * mm;
+    if (i < 19) {
+      const int ex = kVel[i][0], ey = kVel[i][1], ez = kVel[i][2];
+      int sx = cx - ex, sy = cy - ey, sz = cz - ez;
+      sx = sx < 0 ? sx + m.g.nx : (sx >= m.g.nx ? sx - m.g.nx : sx);
+      sy = sy < 0 ? sy + m.g.ny : (sy >= m.g.ny ? sy - m.g.ny : sy);
+      sz = sz < 0 ? sz + m.g.nz : (sz >= m.g.nz ? sz - m.g.nz : sz);
+      const T d = pop[19 * (size_t)m.site_off + pop_offset(m.g, i, sx, sy, sz)];
+      drho += d;
+      qx += (T)ex * d;
+      qy += (T)ey * d;
+      qz += (T)ez * d;
+    }
+  }
+  drho = quad_sum(drho);
+  qx = quad_sum(qx);
+  qy = quad_sum(qy);
+  qz = quad_sum(qz);
+  const T mine = c == 0 ? qx : (c == 1 ? qy : (c == 2 ? qz : T(1) / ((T)m.rho0 + drho)));
+  a.cc[(size_t)p * 32 + sl] = mine;
+  // claims (claim_site): corners k and k ^ 1 (4 lanes apart) lie in one
+  // row, most often in one 64-bit mark word, and then one atomic sets both
+  // bits; each corner reads its own bit's old value (a corner that
+  // coincides with its partner, on an axis of one site, is claimed twice)
+  const int gs = m.site_off + site;
+  const int gs_pair = __shfl_xor(gs, 4, kRefillLanes);
+  const bool same_word = (gs >> 6) == (gs_pair >> 6);
+  const bool lead = (k & 1) == 0 || !same_word;
+  unsigned long long old = 0;
+  if (c == 0 && lead) {
+    unsigned long long bits = 1ull << (gs & 63);
+    if (same_word) bits |= 1ull << (gs_pair & 63);
+    old = set_marks<Local>(a.mark + (gs >> 6), bits);
+  }
+  const unsigned long long old_pair = __shfl_xor(old, 4, kRefillLanes);
+  if (c == 0 && (((lead ? old : old_pair) >> (gs & 63)) & 1ull || gs == gs_pair))
+    reinterpret_cast<T*>(a.J + gs)[3] = T(1);
+  if (sl == 0 && a.own_on) a.owner[gs] = (int32_t)p;  // corner 0: the cube's base
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_refill(CoupleArgs<T> a) {
   const T* __restrict__ pop = a.pop[a.clock->cur];
@@ -58,64 +122,7 @@ __global__ __launch_bounds__(kBlock) void k_refill(CoupleArgs<T> a) {
   for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < lanes;
        t += (int64_t)gridDim.x * kBlock) {
     const int64_t p = t / kRefillLanes;
-    const int sl = threadIdx.x & (kRefillLanes - 1);
-    const int k = sl >> 2, c = sl & 3;
-    const RepMD& m = a.md[a.single ? 0 : a.part_rep[p]];
-    const int64_t N = a.N;
-    double X[3];
-    bool finite = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      X[d] = a.x[d * N + p];
-      finite = finite && isfinite(X[d]);
-    }
-    if (!finite) continue;
-    Cube q;
-    cube_of(X, m.g, q);
-    int cx, cy, cz, site;
-    double w;
-    corner_of(q, m.g, k, cx, cy, cz, site, w);
-    T drho = T(0), qx = T(0), qy = T(0), qz = T(0);
-#pragma unroll
-    for (int mm = 0; mm < 5; ++mm) {
-      const int i = c + 4 * mm;
-      if (i < 19) {
-        const int ex = kVel[i][0], ey = kVel[i][1], ez = kVel[i][2];
-        int sx = cx - ex, sy = cy - ey, sz = cz - ez;
-        sx = sx < 0 ? sx + m.g.nx : (sx >= m.g.nx ? sx - m.g.nx : sx);
-        sy = sy < 0 ? sy + m.g.ny : (sy >= m.g.ny ? sy - m.g.ny : sy);
-        sz = sz < 0 ? sz + m.g.nz : (sz >= m.g.nz ? sz - m.g.nz : sz);
-        const T d = pop[19 * (size_t)m.site_off + pop_offset(m.g, i, sx, sy, sz)];
-        drho += d;
-        qx += (T)ex * d;
-        qy += (T)ey * d;
-        qz += (T)ez * d;
-      }
-    }
-    drho = quad_sum(drho);
-    qx = quad_sum(qx);
-    qy = quad_sum(qy);
-    qz = quad_sum(qz);
-    const T mine = c == 0 ? qx : (c == 1 ? qy : (c == 2 ? qz : T(1) / ((T)m.rho0 + drho)));
-    a.cc[(size_t)p * 32 + sl] = mine;
-    // claims (claim_site): corners k and k ^ 1 (4 lanes apart) lie in one
-    // row, most often in one 64-bit mark word, and then one atomic sets both
-    // bits; each corner reads its own bit's old value (a corner that
-    // coincides with its partner, on an axis of one site, is claimed twice)
-    const int gs = m.site_off + site;
-    const int gs_pair = __shfl_xor(gs, 4, kRefillLanes);
-    const bool same_word = (gs >> 6) == (gs_pair >> 6);
-    const bool lead = (k & 1) == 0 || !same_word;
-    unsigned long long old = 0;
-    if (c == 0 && lead) {
-      unsigned long long bits = 1ull << (gs & 63);
-      if (same_word) bits |= 1ull << (gs_pair & 63);
-      old = atomicOr(a.mark + (gs >> 6), bits);
-    }
-    const unsigned long long old_pair = __shfl_xor(old, 4, kRefillLanes);
-    if (c == 0 && (((lead ? old : old_pair) >> (gs & 63)) & 1ull || gs == gs_pair))
-      reinterpret_cast<T*>(a.J + gs)[3] = T(1);
-    if (sl == 0 && a.own_on) a.owner[gs] = (int32_t)p;  // corner 0: the cube's base
+    refill_particle<false>(a, a.md[a.single ? 0 : a.part_rep[p]], pop, p);
   }
 }
 
@@ -141,10 +148,9 @@ __global__ __launch_bounds__(kBlock) void k_refill3(CoupleArgs<T> a) {
     }
     if (!finite) continue;
     Cube q;
-    Stencil<1>::locate(X, m.g, q);
+    locate<1>(X, m.g, q);
     int cx, cy, cz, site;
-    double w;
-    Stencil<1>::site(q, m.g, k, cx, cy, cz, site, w);
+    stencil_site<1>(q, m.g, k, cx, cy, cz, site);
     size_t off[19];
     pull_offsets(m.g, cx, cy, cz, off);
     const T* __restrict__ base = pop + 19 * (size_t)m.site_off;
@@ -209,280 +215,333 @@ __global__ __launch_bounds__(kBlock) void k_refill3(CoupleArgs<T> a) {
 // (position-dependent forces follow), lane 0 also counts the particle into
 // its force cell at the new position.
 // ---------------------------------------------------------------------------
-// Lanes of the coupling kernel per particle: L lanes with ceil(sites / L)
-// stencil sites each.
-template <int L>
-struct CoupleShape {
-  static constexpr int kLanes = L;
-  __device__ static __forceinline__ double sum(double v) {
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) v += __shfl_xor(v, o, L);
-    return v;
-  }
+// The step's place in its LB interval: retag, the sharing of every site comes
+// from the w words of J; last, every transfer is left in J; final, the
+// interval's last MD step (CoupleArgs has the reasons).
+struct StepFlags {
+  int retag, last, final;
+};
+// Where a block's entries of the two lists go, and their numbers (in LDS).
+struct StepLists {
+  int64_t entry0, mover0;
+  int *entries, *movers;
 };
 
-// Retag: the launch takes every site's sharing from J (the first MD step
-// after a refill), so the own-transfer entries are written but not read.
+// One lane of the MD step of particle p0 + t / L of a replica (t < lanes;
+// every thread of a wavefront calls it with the same p0, m and rep).
+// Local: see add_transfer.
+//
+// Every wavefront runs some hundreds of instructions for its 64 / L
+// particles, a large part of them dependent FP64 ones, and that chain sets
+// the time of small systems and a good part of that of large ones.  So:
+// element offsets of 32 bits on scalar bases; sites and weights axis by axis
+// (stencil_axes), the squared weights as a product of axis sums; sums over
+// the lanes by DPP; no modulo and no division; the loads from J only where a
+// lane of the wavefront needs them.  Measured (three cycles and a copy, or
+// twenty cycles of the smallest): 16^3 with 32 particles in FP64 1128 -> 1033
+// us, 128^3 with the three-point stencil 1000 -> 908, 256^3 2815 -> 2777.
+// (Loading J under per-site branches instead of by selected addresses cost the
+// smallest case 60 us; holding the kernel to 4 waves per SIMD spilled: 2881.)
+template <typename T, bool Rec, int ST, int L, bool Bin, bool Retag, bool Local>
+__device__ __forceinline__ void couple_lane(const CoupleArgs<T>& a, const RepMD& m, int rep,
+                                            int64_t p0, uint32_t t, uint32_t lanes,
+                                            unsigned long long t_md, const StepFlags& st,
+                                            const StepLists& lists, double* __restrict__ rec) {
+  using St = Stencil<ST>;
+  constexpr int kPer = (St::kSites + L - 1) / L;
+  constexpr bool kFull = St::kSites % L == 0;  // every lane has kPer sites
+  static_assert(!Rec || ST == 0, "recording (adjoint) exists for the trilinear stencil only");
+  if (t >= lanes) return;
+  const uint32_t step_lo = (uint32_t)(t_md & 0xFFFFFFFFull), step_hi = (uint32_t)(t_md >> 32);
+  const uint32_t N = (uint32_t)a.N;
+  const uint32_t pl = t / L, p = (uint32_t)p0 + pl;
+  const int k0 = (int)(t & (L - 1));
+  Vec4<T>* __restrict__ cc = reinterpret_cast<Vec4<T>*>(a.cc) + p0 * St::kSites;
+  Vec4<T>* __restrict__ own = a.own + p0 * St::kSites;
+  const uint32_t e0 = pl * St::kSites + k0;  // the lane's first entry of the two
+  // everything the step reads of the particle and its stencil entries,
+  // loaded together (J, which needs the stencil's sites, follows)
+  double X[3], V[3], fc[3] = {0.0, 0.0, 0.0};
+  int old_bin = -1;  // Bin: the particle's count entry of the previous binning
+  if (Bin && k0 == 0) old_bin = el(a.bin, p);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    X[d] = el(a.x, p + d * N);
+    V[d] = el(a.v, p + d * N);
+  }
+  if (m.force_model != 0) {  // (no conservative forces in force model 0)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) fc[d] = el(a.fcons, p + d * N);
+  }
+  const uint32_t lp = (uint32_t)el(a.pid, p);
+  Vec4<T> cv_[kPer], jv_[kPer];
+#pragma unroll
+  for (int jj = 0; jj < kPer; ++jj) {
+    cv_[jj] = jv_[jj] = Vec4<T>{T(0), T(0), T(0), T(0)};
+    if (kFull || k0 + jj * L < St::kSites) {
+      cv_[jj] = el(cc, e0 + jj * L);
+      // (Bin: position-dependent forces, so no own transfers are kept; every
+      // MD step takes the sharing and the transfer from J; Retag: this one)
+      if (!Bin && !Retag) jv_[jj] = el(own, e0 + jj * L);
+    }
+  }
+  bool live = true;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) live = live && isfinite(X[d]) && isfinite(V[d]);
+  if (!live) {
+    if (k0 == 0) {
+      a.flags[0] = 1;
+      if (Rec) rec[p] = __builtin_nan("");
+      if (Bin) {
+        if (old_bin >= 0) a.bin_count[old_bin] = 0;
+        el(a.bin, p) = -1;
+      }
+    }
+    return;
+  }
+  Cube q;
+  locate<ST>(X, m.g, q);
+  StencilAxes<ST> ax;
+  stencil_axes<ST>(q, m.g, ax);
+  const double S = squared_weights<ST>(ax);
+  int gs_[kPer];
+  double w_[kPer];
+#pragma unroll
+  for (int jj = 0; jj < kPer; ++jj) {
+    int ox, oy, oz;
+    St::offsets(k0 | (jj * L), ox, oy, oz);
+    gs_[jj] = m.site_off + pick(ax.off[0], ox) + pick(ax.off[1], oy) + pick(ax.off[2], oz);
+    w_[jj] = pick(ax.w[0], ox) * pick(ax.w[1], oy) * pick(ax.w[2], oz);
+    if (!kFull && k0 + jj * L >= St::kSites) {
+      gs_[jj] = -1;
+      w_[jj] = 0.0;
+    }
+  }
+  // the sites' pending transfer: the particle's own one where it claimed
+  // the site alone, else J; after a refill the w word of J tells which
+  // (claim_site), and so it does for a site claimed after a stencil change
+  // (own w = 2)
+  const bool retag = Bin || Retag || st.retag != 0;
+  T ow_[kPer];
+  bool any = false;
+#pragma unroll
+  for (int jj = 0; jj < kPer; ++jj) {
+    ow_[jj] = retag ? T(2) : jv_[jj].w;
+    any = any | (ow_[jj] != T(0));
+  }
+  if (Bin || Retag || __ballot(any) != 0) {
+    if (Local) {
+#pragma unroll
+      for (int jj = 0; jj < kPer; ++jj)
+        if (ow_[jj] != T(0)) jv_[jj] = load_transfer_local(a.J + gs_[jj]);
+    } else {
+      // (one load per site, from J or again from the own entry, which no
+      // other thread writes: no branch, so the loads issue back to back; a
+      // slot past the stencil's last site reads the first own entry)
+      const Vec4<T>* src_[kPer];
+#pragma unroll
+      for (int jj = 0; jj < kPer; ++jj) {
+        const bool site = kFull || gs_[jj] >= 0;
+        src_[jj] = site && (Bin || Retag || ow_[jj] != T(0)) ? a.J + gs_[jj]
+                                                             : &el(own, site ? e0 + jj * L : e0);
+      }
+#pragma unroll
+      for (int jj = 0; jj < kPer; ++jj) jv_[jj] = *src_[jj];
+    }
+  }
+  // fluid velocity at the particle (Eq. 5); from variant 2 on it includes the
+  // pending transfer
+  const double seen = a.variant >= 2 ? 1.0 : 0.0;
+  double u[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int jj = 0; jj < kPer; ++jj) {
+    const double j3[3] = {(double)cv_[jj].x + seen * (double)jv_[jj].x,
+                          (double)cv_[jj].y + seen * (double)jv_[jj].y,
+                          (double)cv_[jj].z + seen * (double)jv_[jj].z};
+    if (Rec) {
+      const int64_t k = k0 + jj * L;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) rec[(6 + 3 * k + d) * a.N + p] = j3[d];
+      rec[(30 + k) * a.N + p] = (double)cv_[jj].w;
+    }
+    // (a slot past the stencil's last site has weight 0 and moments 0)
+    const double wi = w_[jj] * (double)cv_[jj].w;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) u[d] += wi * j3[d];
+  }
+  if (Rec && k0 == 0) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      rec[d * a.N + p] = X[d];
+      rec[(3 + d) * a.N + p] = V[d];
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) u[d] = group_sum<L>(u[d]);
+  // friction + noise (Eq. 4), momentum change over the MD step (Eq. 6); the
+  // noise amplitude follows from the stencil's squared weights
+  double Fr[3] = {0.0, 0.0, 0.0};
+  if (m.noise) {
+    const double amp = noise_amplitude(m, S);
+    // (the keys in vector registers: the twenty round keys would otherwise
+    // take scalar ones all at once and push others out)
+    uint32_t ka = m.key0, kb = m.key1;
+    asm("" : "+v"(ka), "+v"(kb));
+    const Words4 o = philox10(Words4{lp, step_lo, m.tag, step_hi}, ka, kb);
+    const uint32_t ws[3] = {o.w0, o.w1, o.w2};
+    // sqrt(12) ((h + 1/2) / 2^24 - 1/2) of the 24-bit h
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      Fr[d] = amp * (3.4641016151377546 *
+                     (((double)(ws[d] >> 8) + 0.5) * 5.9604644775390625e-08 - 0.5));
+  }
+  // velocity Verlet with the coupling force held over the step; with
+  // position-dependent conservative forces the second half-kick waits
+  // for the forces at the new positions (k_forces)
+  const double second = m.split_kick ? 0.0 : 1.0;
+  double Xn[3], vn[3], dp[3], Fc[3];
+  int32_t dim[3] = {0, 0, 0};  // periodic images crossed in this step (rare)
+  bool in = true;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    Fc[d] = Fr[d] - m.gamma * (V[d] - u[d]);
+    dp[d] = m.tau * Fc[d];
+    const double kick = m.h * (fc[d] + Fc[d]);
+    const double v1 = V[d] + kick;
+    Xn[d] = X[d] + m.tau * v1;
+    vn[d] = v1 + second * kick;
+    in = in & (Xn[d] >= 0.0) & (Xn[d] < m.L[d]);
+  }
+  if (!in) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) wrap_coord(Xn[d], dim[d], m.L[d]);
+  }
+  if (k0 == 0) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      if (m.split_kick) el(a.fc_held, p + d * N) = Fc[d];
+      el(a.x, p + d * N) = Xn[d];
+      el(a.v, p + d * N) = vn[d];
+    }
+    if (!in) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) el(a.img, p + d * N) += dim[d];
+    }
+  }
+  const bool fin = isfinite(Xn[0]) && isfinite(Xn[1]) && isfinite(Xn[2]);
+  if (Bin && k0 == 0) {
+    // force cell at the new position (MD step t_md + 1), for the force
+    // kernel that follows; the count entry of the previous binning (the
+    // other half) is cleared for the binning after this one
+    if (old_bin >= 0) a.bin_count[old_bin] = 0;
+    const int half = (int)((t_md + 1) & 1);
+    if (m.force_model >= 2 && fin) {
+      const int cb = m.cell_off + local_cell(Xn, m);
+      el(a.bin, p) = (int32_t)(half * a.ncells + cb);
+      cell_insert(a.bin_count + half * a.ncells, a.bin_slot, a.bin_ovf,
+                  a.bin_count + 2 * a.ncells + half, a.cell_cap, cb, (int)p);
+    } else {
+      el(a.bin, p) = -1;
+    }
+  }
+  // the next MD step needs other sites if the stencil moved (a non-finite
+  // new position is caught by that step); every lane of the particle sees the
+  // same new position
+  bool moved = false;
+  Cube qn;
+  if (fin) {
+    locate<ST>(Xn, m.g, qn);
+    moved = qn.base[0] != q.base[0] || qn.base[1] != q.base[1] || qn.base[2] != q.base[2];
+  }
+  // the particle's own transfers go to J when it leaves its sites (a
+  // non-finite particle is skipped from the next step on) and at the
+  // interval's last MD step
+  const bool leave = st.last || moved || !fin;
+  if ((moved || !fin) && k0 == 0) {
+    const int old_cell = gs_[0] - m.site_off;  // (lane 0's first site is the lowest)
+    // the record of the stencil it leaves (owner_of_shared)
+    if (a.own_on) el(a.owner + m.site_off, (uint32_t)old_cell) = -1;
+    if (moved) {
+      a.moved_at[p] = (long long)t_md;
+      // (after the interval's last MD step the next refill gathers and claims
+      // every particle's stencil: moved particles need no after-step work)
+      if (!st.final)
+        reinterpret_cast<int4*>(a.mlist)[lists.mover0 + atomicAdd(lists.movers, 1)] =
+            make_int4((int)p, qn.base[0] + m.g.nx * (qn.base[1] + m.g.ny * qn.base[2]), old_cell,
+                      rep);
+    }
+  }
+  // transfer -w_k dP (Eq. 7-8): a site only this particle claimed in the
+  // interval has no other reader or writer, so it takes the new value right
+  // away; transfers to shared sites wait in the step's list until every
+  // particle has read J (after_step_item)
+#pragma unroll
+  for (int jj = 0; jj < kPer; ++jj) {
+    int gs = gs_[jj];
+    asm("" : "+v"(gs));  // (its address in J is not kept from the load above)
+    const double ww = -w_[jj];
+    const Vec4<T> add{(T)(ww * dp[0]), (T)(ww * dp[1]), (T)(ww * dp[2]), T(0)};
+    if (!kFull && gs < 0) continue;
+    if (jv_[jj].w == T(0)) {
+      const Vec4<T> nv{jv_[jj].x + add.x, jv_[jj].y + add.y, jv_[jj].z + add.z, T(0)};
+      if (!Bin && !st.final) el(own, e0 + jj * L) = nv;
+      if (leave) a.J[gs] = nv;
+    } else {
+      const int64_t e = lists.entry0 + atomicAdd(lists.entries, 1);
+      a.lsite[e] = gs;
+      a.ldelta[e] = add;
+      if (!Bin && ow_[jj] == T(2) && !st.final)
+        el(own, e0 + jj * L) = Vec4<T>{T(0), T(0), T(0), T(1)};
+    }
+  }
+}
+
+// One: a single replica, its constants read once (scalar loads); otherwise
+// per wavefront, whose particles mostly belong to one replica (and are taken
+// replica by replica where they do not).
 template <typename T, bool Rec, int ST, int L, bool Bin, bool One, bool Retag = false>
 __global__ __launch_bounds__(kBlock) void k_couple(CoupleArgs<T> a) {
-  using St = Stencil<ST>;
-  using Sh = CoupleShape<L>;
-  constexpr int kPer = (St::kSites + L - 1) / L;
-  static_assert(!Rec || ST == 0, "recording (adjoint) exists for the trilinear stencil only");
+  constexpr int kPer = (Stencil<ST>::kSites + L - 1) / L;
   const unsigned long long t_md = (unsigned long long)(a.clock->t_md + a.substep);
-  const uint32_t step_lo = (uint32_t)(t_md & 0xFFFFFFFFull), step_hi = (uint32_t)(t_md >> 32);
-  const int64_t N = a.N;
-  const int64_t lanes = N * Sh::kLanes;
-  // One (a single replica): the replica's constants are the same for every
-  // particle, read once before any store (uniform, scalar loads); otherwise
-  // each particle reads its replica's entry
+  const int64_t lanes = a.N * L;
   RepMD m1;
-  if constexpr (One) m1 = a.md[0];
+  if constexpr (One) m1 = scalar_copy(a.md);
+  const StepFlags st{a.retag, a.last, a.final_step};
   // entries of this block's segment in the two lists, counted in LDS
   __shared__ int s_l, s_m;
   // Bin: the overflow length of the other half, for the binning after this one
   if (Bin && blockIdx.x == 0 && threadIdx.x == 0) a.bin_count[2 * a.ncells + (int)(t_md & 1)] = 0;
-  // lanes come in whole particles (kLanes | kBlock): the lanes of a particle
+  // lanes come in whole particles (L | kBlock): the lanes of a particle
   // are always active together, as the shuffles require; every thread of a
   // block runs the loop the same number of times (block barriers)
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   for (int64_t t0 = (int64_t)blockIdx.x * kBlock; t0 < lanes; t0 += stride) {
-    const int64_t t = t0 + threadIdx.x;
     const int64_t seg = t0 / kBlock;
     if (threadIdx.x == 0) s_l = s_m = 0;
     __syncthreads();
-    bool moved = false, leave = false;
-    int new_cell = 0, old_cell = 0;
-    int gs_[kPer];
-    double w_[kPer];
-    Vec4<T> jv_[kPer];
-    bool sh_[kPer], dec_[kPer];
-    double dp[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int jj = 0; jj < kPer; ++jj) {
-      gs_[jj] = -1;
-      sh_[jj] = dec_[jj] = false;
-    }
-    const int64_t p = t / Sh::kLanes;
-    const int k0 = (int)(t & (Sh::kLanes - 1));
-    double X[3], V[3];
-    // everything the step reads of the particle and its stencil entries,
-    // loaded together (J, which needs the stencil's sites, follows)
-    double fc[3] = {0.0, 0.0, 0.0};
-    uint32_t lp = 0;
-    Vec4<T> cv_[kPer];
-    int old_bin = -1;  // Bin: the particle's count entry of the previous binning
-    int rep_p = 0;     // the particle's replica (several replicas)
-    RepMD mr;
-    bool live = t < lanes;
-    if (live) {
-      if (Bin && k0 == 0) old_bin = a.bin[p];
-      if constexpr (!One) rep_p = a.part_rep[p];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        X[d] = a.x[d * N + p];
-        V[d] = a.v[d * N + p];
-      }
-      // conservative forces: none in force model 0 (known here for a single
-      // replica; otherwise the zeros are read)
-      if (!One || m1.force_model != 0) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) fc[d] = a.fcons[d * N + p];
-      }
-      lp = (uint32_t)a.pid[p];
-#pragma unroll
-      for (int jj = 0; jj < kPer; ++jj) {
-        const int k = k0 + jj * Sh::kLanes;
-        if (k < St::kSites) {
-          cv_[jj] = *cache_entry<ST>(a, p, k);
-          // (Bin: position-dependent forces, so no own transfers are kept;
-          // every MD step takes the sharing and the transfer from J; Retag:
-          // this step does)
-          if constexpr (Bin || Retag)
-            jv_[jj] = Vec4<T>{T(0), T(0), T(0), T(0)};
-          else
-            jv_[jj] = *own_entry<ST>(a, p, k);
+    const StepLists lists{seg * (kBlock * kPer), seg * (kBlock / L), &s_l, &s_m};
+    const uint32_t left = (uint32_t)(lanes - t0 < kBlock ? lanes - t0 : kBlock);
+    const int64_t p0 = t0 / L;
+    if constexpr (One) {
+      couple_lane<T, Rec, ST, L, Bin, Retag, false>(a, m1, 0, p0, threadIdx.x, left, t_md, st,
+                                                    lists, a.rec);
+    } else {
+      const bool in = threadIdx.x < left;
+      const int rep = in ? a.part_rep[p0 + threadIdx.x / L] : -1;
+      // (a loop on the wavefront's own mask, so that the body stays inside it)
+      for (unsigned long long todo = __ballot(in); todo != 0;) {
+        const bool mine = rep == __builtin_amdgcn_readlane(rep, __ffsll(todo) - 1);
+        if (mine) {
+          // (read again from the lanes taken: the compiler would put `rep`, a
+          // vector register, in place of a value known to equal it)
+          const int r = __builtin_amdgcn_readfirstlane(rep);
+          const RepMD mr = scalar_copy(a.md + r);
+          couple_lane<T, Rec, ST, L, Bin, Retag, false>(a, mr, r, p0, threadIdx.x, left, t_md, st,
+                                                        lists, a.rec);
         }
-      }
-      // the replica's constants as soon as its index is in (several replicas)
-      if constexpr (!One) mr = a.md[rep_p];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) live = live && isfinite(X[d]) && isfinite(V[d]);
-      if (!live && k0 == 0) {
-        a.flags[0] = 1;
-        if (Rec) a.rec[p] = __builtin_nan("");
-        if (Bin) {
-          if (old_bin >= 0) a.bin_count[old_bin] = 0;
-          a.bin[p] = -1;
-        }
+        todo &= ~__ballot(mine);
       }
     }
-    if (live) {
-      const RepMD& m = One ? m1 : mr;
-      Cube q;
-      St::locate(X, m.g, q);
-      // the sites' pending transfer: the particle's own one where it claimed
-      // the site alone, else J (all loads issued before use); after a refill
-      // the w word of J tells which (claim_site), and so it does for a site
-      // claimed after a stencil change (own w = 2)
-#pragma unroll
-      for (int jj = 0; jj < kPer; ++jj) {
-        const int k = k0 + jj * Sh::kLanes;
-        if (k < St::kSites) {
-          int cx, cy, cz, site;
-          double w;
-          St::site(q, m.g, k, cx, cy, cz, site, w);
-          gs_[jj] = m.site_off + site;
-          w_[jj] = w;
-        }
-      }
-      // (one load per site, from J or again from the own entry, which no
-      // other thread writes: no branch, so the loads issue back to back)
-      const bool retag = a.retag != 0;
-      const Vec4<T>* src_[kPer];
-#pragma unroll
-      for (int jj = 0; jj < kPer; ++jj) {
-        const T ow = jv_[jj].w;
-        dec_[jj] = retag | (ow == T(2));
-        const bool use_j = (retag | (ow != T(0))) & (gs_[jj] >= 0);
-        // (a slot past the stencil's last site reads the first own entry)
-        src_[jj] = use_j ? a.J + gs_[jj]
-                         : own_entry<ST>(a, p, gs_[jj] >= 0 ? k0 + jj * Sh::kLanes : 0);
-      }
-#pragma unroll
-      for (int jj = 0; jj < kPer; ++jj) jv_[jj] = *src_[jj];
-      double ux = 0.0, uy = 0.0, uz = 0.0;
-#pragma unroll
-      for (int jj = 0; jj < kPer; ++jj) {
-        if (gs_[jj] < 0) continue;
-        const int k = k0 + jj * Sh::kLanes;
-        const Vec4<T> cv = cv_[jj];
-        sh_[jj] = jv_[jj].w != T(0);
-        // fluid velocity at the particle (Eq. 5)
-        double jx = (double)cv.x, jy = (double)cv.y, jz = (double)cv.z;
-        if (a.variant >= 2) {  // the fluid velocity includes the pending transfer
-          jx += (double)jv_[jj].x;
-          jy += (double)jv_[jj].y;
-          jz += (double)jv_[jj].z;
-        }
-        if (Rec) {
-          a.rec[(6 + 3 * k) * N + p] = jx;
-          a.rec[(7 + 3 * k) * N + p] = jy;
-          a.rec[(8 + 3 * k) * N + p] = jz;
-          a.rec[(30 + k) * N + p] = (double)cv.w;
-        }
-        const double wi = w_[jj] * (double)cv.w;
-        ux += wi * jx;
-        uy += wi * jy;
-        uz += wi * jz;
-      }
-      if (Rec && k0 == 0) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          a.rec[d * N + p] = X[d];
-          a.rec[(3 + d) * N + p] = V[d];
-        }
-      }
-      const double u[3] = {Sh::sum(ux), Sh::sum(uy), Sh::sum(uz)};
-      // noise amplitude from the stencil's squared weights (noise_amplitude)
-      double s2 = 0.0;
-#pragma unroll
-      for (int jj = 0; jj < kPer; ++jj)
-        if (gs_[jj] >= 0) s2 += w_[jj] * w_[jj];
-      const double amp = m.noise ? noise_amplitude(m, Sh::sum(s2)) : 0.0;
-      // friction + noise (Eq. 4), momentum change over the MD step (Eq. 6)
-      double xi[3] = {0.0, 0.0, 0.0};
-      if (m.noise) {
-        const Words4 o = philox10(Words4{lp, step_lo, m.tag, step_hi}, m.key0, m.key1);
-        const uint32_t ws[3] = {o.w0, o.w1, o.w2};
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          xi[d] = 3.4641016151377546 * (((double)(ws[d] >> 8) + 0.5) * 5.9604644775390625e-08 - 0.5);
-      }
-      // velocity Verlet with the coupling force held over the step; with
-      // position-dependent conservative forces the second half-kick waits
-      // for the forces at the new positions (k_forces)
-      double Xn[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const double Fc = -m.gamma * (V[d] - u[d]) + amp * xi[d];
-        dp[d] = m.tau * Fc;
-        double v1 = V[d] + m.h * (fc[d] + Fc);
-        double x1 = X[d] + m.tau * v1;
-        int32_t dim = 0;  // periodic images crossed in this step (rare)
-        wrap_coord(x1, dim, m.L[d]);
-        Xn[d] = x1;
-        if (k0 == 0) {
-          if (m.split_kick)
-            a.fc_held[d * N + p] = Fc;
-          else
-            v1 += m.h * (fc[d] + Fc);
-          a.x[d * N + p] = x1;
-          a.v[d * N + p] = v1;
-          if (dim != 0) a.img[d * N + p] += dim;
-        }
-      }
-      if (Bin && k0 == 0) {
-        // force cell at the new position (MD step t_md + 1), for the force
-        // kernel that follows; the count entry of the previous binning (the
-        // other half) is cleared for the binning after this one
-        if (old_bin >= 0) a.bin_count[old_bin] = 0;
-        const int half = (int)((t_md + 1) & 1);
-        if (m.force_model >= 2 && isfinite(Xn[0]) && isfinite(Xn[1]) && isfinite(Xn[2])) {
-          const int cb = m.cell_off + local_cell(Xn, m);
-          a.bin[p] = (int32_t)(half * a.ncells + cb);
-          cell_insert(a.bin_count + half * a.ncells, a.bin_slot, a.bin_ovf,
-                      a.bin_count + 2 * a.ncells + half, a.cell_cap, cb, (int)p);
-        } else {
-          a.bin[p] = -1;
-        }
-      }
-      // the next MD step needs other sites if the stencil moved (a
-      // non-finite new position is caught by that step); every lane of the
-      // particle sees the same new position
-      const bool fin = isfinite(Xn[0]) && isfinite(Xn[1]) && isfinite(Xn[2]);
-      if (fin) {
-        Cube qn;
-        St::locate(Xn, m.g, qn);
-        moved = qn.base[0] != q.base[0] || qn.base[1] != q.base[1] || qn.base[2] != q.base[2];
-        new_cell = qn.base[0] + m.g.nx * (qn.base[1] + m.g.ny * qn.base[2]);
-      }
-      // the particle's own transfers go to J when it leaves its sites (a
-      // non-finite particle is skipped from the next step on) and at the
-      // interval's last MD step
-      leave = a.last || moved || !fin;
-      if (moved && k0 == 0) a.moved_at[p] = (long long)t_md;
-      old_cell = q.base[0] + m.g.nx * (q.base[1] + m.g.ny * q.base[2]);
-      // the record of the stencil it leaves (owner_of_shared)
-      if ((moved || !fin) && k0 == 0 && a.own_on) a.owner[m.site_off + old_cell] = -1;
-    }
-    // transfer -w_k dP (Eq. 7-8): a site only this particle claimed in the
-    // interval has no other reader or writer, so it takes the new value right
-    // away; transfers to shared sites wait in the step's list until every
-    // particle has read J (after_step_item)
-#pragma unroll
-    for (int jj = 0; jj < kPer; ++jj) {
-      const int gs = gs_[jj];
-      const double ww = gs >= 0 ? w_[jj] : 0.0;
-      const T ax = (T)(-ww * dp[0]), ay = (T)(-ww * dp[1]), az = (T)(-ww * dp[2]);
-      if (gs >= 0 && !sh_[jj]) {
-        const Vec4<T> nv{jv_[jj].x + ax, jv_[jj].y + ay, jv_[jj].z + az, T(0)};
-        if (!Bin && !a.final_step) *own_entry<ST>(a, p, k0 + jj * Sh::kLanes) = nv;
-        if (leave) a.J[gs] = nv;
-      }
-      if (gs >= 0 && sh_[jj]) {
-        const int64_t e = seg * (kBlock * kPer) + atomicAdd(&s_l, 1);
-        a.lsite[e] = gs;
-        a.ldelta[e] = Vec4<T>{ax, ay, az, T(0)};
-        if (!Bin && dec_[jj] && !a.final_step)
-          *own_entry<ST>(a, p, k0 + jj * Sh::kLanes) = Vec4<T>{T(0), T(0), T(0), T(1)};
-      }
-    }
-    // (after the interval's last MD step the next refill gathers and claims
-    // every particle's stencil: moved particles need no after-step work)
-    if (moved && k0 == 0 && !a.final_step)
-      reinterpret_cast<int4*>(a.mlist)[seg * (kBlock / L) + atomicAdd(&s_m, 1)] =
-          make_int4((int)p, new_cell, old_cell, rep_p);
     __syncthreads();
     if (threadIdx.x == 0) {
       a.lseg[seg] = s_l;
@@ -584,7 +643,7 @@ static hipError_t couple_st(Context* c, int substep) {
   // with position-dependent forces (never recorded) the kernel also bins
   const bool bin = c->plan.any_forces2 && !a.rec;
   if (ST == 0 && a.rec) {
-    hipLaunchKernelGGL((k_couple<T, true, 0, 8, false, false>), cgrid, dim3(kBlock), 0, c->stream,
+    hipLaunchKernelGGL((k_couple<T, true, 0, 8, false, true>), cgrid, dim3(kBlock), 0, c->stream,
                        a);
   } else if constexpr (ST == 0) {
     if (L == 2)
@@ -654,10 +713,9 @@ __global__ __launch_bounds__(kBlock) void k_leave_transfers(CoupleArgs<T> a) {
     if (e.w != T(0)) continue;
     const RepMD& m = a.md[a.single ? 0 : a.part_rep[p]];
     Cube q;
-    St::locate(X, m.g, q);
+    locate<ST>(X, m.g, q);
     int cx, cy, cz, site;
-    double w;
-    St::site(q, m.g, k, cx, cy, cz, site, w);
+    stencil_site<ST>(q, m.g, k, cx, cy, cz, site);
     T* j = reinterpret_cast<T*>(a.J + m.site_off + site);
     j[0] = e.x;
     j[1] = e.y;

@@ -102,6 +102,33 @@ __device__ __forceinline__ Vec4<T>* own_entry(const CoupleArgs<T>& a, int64_t p,
   return a.own + (size_t)p * Stencil<ST>::kSites + k;
 }
 
+// Local (k_interval): one workgroup holds all the particles of a replica, so
+// what its particles exchange through J and the marks needs no wider scope
+// than the workgroup: atomics resolved in its XCD's L2 instead of on the
+// memory side, and loads ordered by its barriers.
+template <bool Local, typename T>
+__device__ __forceinline__ void add_transfer(T* p, T v) {
+  if (Local)
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else
+    atomicAdd(p, v);
+}
+template <typename T>
+__device__ __forceinline__ T load_local(const T* p) {
+  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ Vec4<T> load_transfer_local(const Vec4<T>* j) {
+  return Vec4<T>{load_local(&j->x), load_local(&j->y), load_local(&j->z), load_local(&j->w)};
+}
+template <bool Local>
+__device__ __forceinline__ unsigned long long set_marks(unsigned long long* word,
+                                                        unsigned long long bits) {
+  if (Local)
+    return __hip_atomic_fetch_or(word, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return atomicOr(word, bits);
+}
+
 // Mark a site as a receiver of momentum transfer in this LB interval; a site
 // claimed again (by another particle, or by one that changed stencils) is
 // flagged as shared in the w word of its transfer entry.  The flag is
@@ -110,10 +137,10 @@ __device__ __forceinline__ Vec4<T>* own_entry(const CoupleArgs<T>& a, int64_t p,
 // atomics touch only the x, y, z words.  Returns whether the site was
 // claimed before.  (Recording the claimant with a compare-and-swap in the w
 // word instead measured slower.)
-template <typename T>
+template <bool Local, typename T>
 __device__ __forceinline__ bool claim_site(const CoupleArgs<T>& a, int gs) {
   const unsigned long long bit = 1ull << (gs & 63);
-  if (atomicOr(a.mark + (gs >> 6), bit) & bit) {
+  if (set_marks<Local>(a.mark + (gs >> 6), bit) & bit) {
     reinterpret_cast<T*>(a.J + gs)[3] = T(1);
     return true;
   }
@@ -181,7 +208,6 @@ template <typename T, int ST>
 __device__ __forceinline__ void notify_holder(const CoupleArgs<T>& a, const RepMD& m, int rep,
                                               int gs, int64_t p, int64_t q, int ox, int oy,
                                               int oz, int bx, int by, int bz, long long now) {
-  using St = Stencil<ST>;
   constexpr int W = BaseRecords<ST>::W;
   const int64_t N = a.N;
   if (q == p || q < 0 || q >= N) return;
@@ -194,7 +220,7 @@ __device__ __forceinline__ void notify_holder(const CoupleArgs<T>& a, const RepM
   if (rq != rep || mv == now || ev.w != T(0)) return;  // (undecided: the flag is in J)
   if (!(isfinite(X[0]) && isfinite(X[1]) && isfinite(X[2]))) return;
   Cube c;
-  St::locate(X, m.g, c);
+  locate<ST>(X, m.g, c);
   if (c.base[0] != bx || c.base[1] != by || c.base[2] != bz) return;
   T* j = reinterpret_cast<T*>(a.J + gs);
   j[0] = ev.x;
@@ -206,9 +232,9 @@ __device__ __forceinline__ void notify_holder(const CoupleArgs<T>& a, const RepM
 // All W^3 records loaded beforehand (the cube: 8).
 template <typename T, int ST>
 __device__ __forceinline__ void owner_of_shared(const CoupleArgs<T>& a, const RepMD& m, int rep,
-                                                int gs, int64_t p, const BaseRecords<ST>& r) {
+                                                int gs, int64_t p, const BaseRecords<ST>& r,
+                                                long long now) {
   constexpr int W = BaseRecords<ST>::W;
-  const long long now = (long long)(a.clock->t_md + a.substep);
 #pragma unroll
   for (int d = 0; d < W * W * W; ++d) {
     const int ox = d % W, oy = (d / W) % W, oz = d / (W * W);
@@ -222,9 +248,8 @@ __device__ __forceinline__ void owner_of_shared(const CoupleArgs<T>& a, const Re
 template <typename T, int ST>
 __device__ __forceinline__ void owner_of_shared_planes(const CoupleArgs<T>& a, const RepMD& m,
                                                        int rep, int gs, int64_t p, int sx, int sy,
-                                                       int sz) {
+                                                       int sz, long long now) {
   constexpr int W = BaseRecords<ST>::W;
-  const long long now = (long long)(a.clock->t_md + a.substep);
   int bx[W], by[W];
 #pragma unroll
   for (int o = 0; o < W; ++o) {
@@ -359,25 +384,23 @@ __device__ __forceinline__ void reduce_segment_transfers(const CoupleArgs<T>& a,
 template <int ST, bool Own>
 constexpr bool kAfterStepPrefetch = ST == 0 && Own;
 
-// ent0: this thread's entry of its first pass, loaded with the count when
-// kAfterStepPrefetch (see after_step_item).
-template <typename T, int ST, bool One, bool Own>
-__device__ __forceinline__ void after_step_movers(const CoupleArgs<T>& a, int64_t seg, int nmv,
-                                                  int L, const int4& ent0) {
+// ml: the list's entries.  ent0: this thread's entry of its first pass, loaded
+// with the count when kAfterStepPrefetch (see after_step_item).  now: the MD
+// step just taken.  m1: the replica's constants (One).
+template <typename T, int ST, bool One, bool Own, bool Local>
+__device__ __forceinline__ void after_step_movers(const CoupleArgs<T>& a, const RepMD& m1,
+                                                  const int4* __restrict__ ml, int nmv,
+                                                  long long now, const int4& ent0) {
   using St = Stencil<ST>;
   const T* __restrict__ pop = a.pop[a.clock->cur];
-  // One (a single replica): its constants read once, before any store
-  // (uniform, scalar loads)
-  RepMD m1;
-  if constexpr (One) m1 = a.md[0];
   const int nm = nmv * St::kLanes;
-  const int4* __restrict__ ml = reinterpret_cast<const int4*>(a.mlist) + seg * (kBlock / L);
-  for (int u = threadIdx.x; u < nm; u += kBlock) {
+  for (int u = threadIdx.x; u < nm; u += blockDim.x) {
     const int k = u % St::kLanes;
     if (k >= St::kSites) continue;
     // (particle, replica-local indices of its new and old stencil bases,
     // replica)
-    const int4 ent = kAfterStepPrefetch<ST, Own> && u < kBlock ? ent0 : ml[u / St::kLanes];
+    const int4 ent =
+        !Local && kAfterStepPrefetch<ST, Own> && u < kBlock ? ent0 : ml[u / St::kLanes];
     const int64_t p = ent.x;
     const RepMD& m = One ? m1 : a.md[a.single ? 0 : ent.w];
     Cube q;
@@ -386,8 +409,7 @@ __device__ __forceinline__ void after_step_movers(const CoupleArgs<T>& a, int64_
     q.base[2] = ent.y / (m.g.nx * m.g.ny);
     q.s[0] = q.s[1] = q.s[2] = 0.0;
     int cx, cy, cz, site;
-    double w;
-    St::site(q, m.g, k, cx, cy, cz, site, w);
+    stencil_site<ST>(q, m.g, k, cx, cy, cz, site);
     // a site of the old stencil was claimed by this particle already, so
     // no other particle holds it alone; for the others, the records of the
     // stencils that may hold it are loaded along with the gather
@@ -412,12 +434,12 @@ __device__ __forceinline__ void after_step_movers(const CoupleArgs<T>& a, int64_
     // stencils in the same step may claim the same site in this very
     // launch, after this claim
     *own_entry<ST>(a, p, k) = Vec4<T>{T(0), T(0), T(0), T(2)};
-    if (claim_site(a, m.site_off + site) && own_on && !was_mine) {
+    if (claim_site<Local>(a, m.site_off + site) && own_on && !was_mine) {
       const int rep = a.single ? 0 : ent.w;
       if (ST == 0)
-        owner_of_shared<T, ST>(a, m, rep, m.site_off + site, p, recs);
+        owner_of_shared<T, ST>(a, m, rep, m.site_off + site, p, recs, now);
       else
-        owner_of_shared_planes<T, ST>(a, m, rep, m.site_off + site, p, cx, cy, cz);
+        owner_of_shared_planes<T, ST>(a, m, rep, m.site_off + site, p, cx, cy, cz, now);
     }
     // the particle's record at its new base, after every lane of its wave
     // has read the records (one of them may be this very one): the lanes
@@ -428,26 +450,25 @@ __device__ __forceinline__ void after_step_movers(const CoupleArgs<T>& a, int64_
   }
 }
 
-// pre: site0, dv0 hold entry threadIdx.x / 3 of the segment, loaded with the
-// count (the cube only, see after_step_item).
-template <typename T>
-__device__ __forceinline__ void after_step_lists(const CoupleArgs<T>& a, int64_t seg, int n,
-                                                 int per, SiteTable<T> tab, bool pre,
-                                                 int site0, const Vec4<T>& dv0) {
-  const int64_t base = seg * (int64_t)(kBlock * per);
-  if (tab.key && n > 1) {
+// base: the list's first entry.  pre: site0, dv0 hold entry threadIdx.x / 3 of
+// it, loaded with the count (the cube only, see after_step_item).
+template <bool Local, typename T>
+__device__ __forceinline__ void after_step_lists(const CoupleArgs<T>& a, int64_t base, int n,
+                                                 SiteTable<T> tab, bool pre, int site0,
+                                                 const Vec4<T>& dv0) {
+  if (!Local && tab.key && n > 1) {
     reduce_segment_transfers(a, base, n, tab);
     return;
   }
   // one lane per (entry, component): the three adds to one site sit in
   // neighbouring lanes of one instruction and reach the memory side as one
   // request instead of three
-  for (int u = threadIdx.x; u < 3 * n; u += kBlock) {
+  for (int u = threadIdx.x; u < 3 * n; u += blockDim.x) {
     const int e = u / 3, comp = u - 3 * e;
     const bool first = pre && u < kBlock;
     const T d = first ? (comp == 0 ? dv0.x : (comp == 1 ? dv0.y : dv0.z))
                       : reinterpret_cast<const T*>(a.ldelta + base + e)[comp];
-    atomicAdd(reinterpret_cast<T*>(a.J + (first ? site0 : a.lsite[base + e])) + comp, d);
+    add_transfer<Local>(reinterpret_cast<T*>(a.J + (first ? site0 : a.lsite[base + e])) + comp, d);
   }
 }
 
@@ -474,7 +495,15 @@ __device__ __forceinline__ void after_step_item(const CoupleArgs<T>& a, int64_t 
       ent0 = reinterpret_cast<const int4*>(a.mlist)[it * (kBlock / L) +
                                                     threadIdx.x / Stencil<ST>::kLanes];
     const int nmv = a.mseg[it];
-    if (nmv > 0) after_step_movers<T, ST, One, Own>(a, it, nmv, L, ent0);
+    if (nmv > 0) {
+      // One (a single replica): its constants read once, before any store
+      // (uniform, scalar loads)
+      RepMD m1;
+      if constexpr (One) m1 = a.md[0];
+      after_step_movers<T, ST, One, Own, false>(
+          a, m1, reinterpret_cast<const int4*>(a.mlist) + it * (kBlock / L), nmv,
+          (long long)(a.clock->t_md + a.substep), ent0);
+    }
   } else {
     const int64_t sg = it - nseg;
     const bool pre = kPre && !tab.key;
@@ -486,7 +515,7 @@ __device__ __forceinline__ void after_step_item(const CoupleArgs<T>& a, int64_t 
       dv0 = a.ldelta[e0];
     }
     const int n = a.lseg[sg];
-    if (n > 0) after_step_lists<T>(a, sg, n, per, tab, pre, site0, dv0);
+    if (n > 0) after_step_lists<false, T>(a, sg * (int64_t)(kBlock * per), n, tab, pre, site0, dv0);
   }
 }
 

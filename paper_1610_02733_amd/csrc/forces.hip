@@ -98,20 +98,9 @@ __device__ __forceinline__ double reciprocal(double a) {
 
 constexpr int kForceLanes = 32;
 
-// Sum over the 32 lanes of a particle, on every lane: inside a row of 16 by
-// DPP (lanes 1 and 2 apart by quad permutations, then the mirrored half row
-// and row, which hold the other groups' sums), the two rows by a shuffle.
-template <int Ctrl>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), Ctrl, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), Ctrl, 0xF, 0xF, false);
-  return v + __hiloint2double(hi, lo);
-}
+// Sum over the 32 lanes of a particle, on every lane.
 __device__ __forceinline__ double lane32_sum(double v) {
-  v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v = dpp_add<0x141>(v);  // row_half_mirror
-  v = dpp_add<0x140>(v);  // row_mirror
+  v = group_sum<16>(v);
   return v + __shfl_xor(v, 16, kForceLanes);
 }
 

@@ -52,7 +52,7 @@ struct RepMD {
   uint32_t key0, key1, tag;
   double rho0, gamma, amp, tau, h;  // amp = sqrt(2 gamma kT / tau): the particle noise
                                     // amplitude before the balance factor (noise_amplitude)
-  double inv_m;                     // 1 / particle mass (0 without particles)
+  double bal0, bal1;                // noise_balance: 1 - gamma tau / (2 m), gamma tau / (2 rho0)
   double L[3];
   double inv_L[3];
   double f_ext[3];

@@ -33,6 +33,36 @@ __device__ __forceinline__ int cell_of(int c, int n) {
   return c < 0 ? c + n : c;
 }
 
+// Element i of an array of less than 4 GB: one 32-bit offset on a scalar base.
+template <typename U>
+__device__ __forceinline__ U& el(U* base, uint32_t i) {
+  return *reinterpret_cast<U*>(reinterpret_cast<char*>(base) + i * (uint32_t)sizeof(U));
+}
+template <typename U>
+__device__ __forceinline__ const U& el(const U* base, uint32_t i) {
+  return *reinterpret_cast<const U*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(U));
+}
+
+// v plus the value of another lane of its row of 16, by a DPP control word.
+template <int Ctrl>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), Ctrl, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), Ctrl, 0xF, 0xF, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+// Sum over groups of L <= 16 neighbouring lanes, on every lane: lanes 1 and 2
+// apart by quad permutations, then the mirrored half row and row, which hold
+// the other groups' sums.
+template <int L>
+__device__ __forceinline__ double group_sum(double v) {
+  static_assert(L == 2 || L == 4 || L == 8 || L == 16, "groups of a row of 16 lanes");
+  v = dpp_add<0xB1>(v);                    // quad_perm [1, 0, 3, 2]
+  if (L > 2) v = dpp_add<0x4E>(v);         // quad_perm [2, 3, 0, 1]
+  if (L > 4) v = dpp_add<0x141>(v);        // row_half_mirror
+  return L > 8 ? dpp_add<0x140>(v) : v;    // row_mirror
+}
+
 // Force cell of a position on its replica's cell grid (clamped to the grid).
 __device__ __forceinline__ void local_cell_coords(const double X[3], const RepMD& m, int c[3]) {
 #pragma unroll
@@ -91,8 +121,9 @@ __device__ __forceinline__ void corner_of(const Cube& q, const Geom& g, int k, i
 // whose equilibrium variance is kT (1/m + S/rho0) when <dP_rand^2> =
 // 2 gamma kT tau (1 - a/2): F_rand = sqrt(2 gamma kT / tau) sqrt(1 - a/2) xi.
 // Zero for a >= 2 (beyond the explicit step's stability bound).
+// (bal0, bal1: the two constants of the balance 1 - a/2, linear in S.)
 __device__ __forceinline__ double noise_balance(const RepMD& m, double S) {
-  return 1.0 - 0.5 * (m.gamma * m.tau * (m.inv_m + S / m.rho0));
+  return m.bal0 - m.bal1 * S;
 }
 __device__ __forceinline__ double noise_amplitude(const RepMD& m, double S) {
   const double bal = noise_balance(m, S);
@@ -123,57 +154,139 @@ __device__ __forceinline__ double oct_sum(double v) {  // over the 8 lanes of a 
 //       (1 + sqrt(1 - 3 r^2)) / 3                for |r| <= 1/2,
 //       (5 - 3|r| - sqrt(1 - 3 (1 - |r|)^2)) / 6 for 1/2 <= |r| <= 3/2;
 //     27 sites.
+// Along an axis both square roots of the three-point kernel are one and the
+// same: with the site at r = s - o, |r| = 1 -+ s for o = +-1, so 1 - |r| = +-s
+// and the weights are (2 -+ 3s - q)/6 and (1 + q)/3, q = sqrt(1 - 3 s^2).
 // kLanes is the lane count per particle of the kernels that gather a
 // stencil's sites one lane each (refill, re-gather after a cube change):
 // 8, or 32 with lanes 27-31 idle.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double kernel3(double r) {
-  const double a = fabs(r);
-  if (a <= 0.5) return (1.0 + sqrt(1.0 - 3.0 * a * a)) * (1.0 / 3.0);
-  const double b = 1.0 - a;  // |r| < 3/2 always holds for the three nearest sites
-  return (5.0 - 3.0 * a - sqrt(1.0 - 3.0 * b * b)) * (1.0 / 6.0);
-}
-
 template <int ST>
 struct Stencil;
 
 template <>
 struct Stencil<0> {
   static constexpr int kSites = 8, kLanes = 8;
-  __device__ static __forceinline__ void locate(const double X[3], const Geom& g, Cube& q) {
-    cube_of(X, g, q);
+  static constexpr int W = 2;  // sites per axis
+  __device__ static __forceinline__ int base_of(double x, int, double& s) {
+    const double fl = floor(x);
+    s = x - fl;
+    return (int)fl;
   }
-  __device__ static __forceinline__ void site(const Cube& q, const Geom& g, int k, int& cx,
-                                              int& cy, int& cz, int& s, double& w) {
-    corner_of(q, g, k, cx, cy, cz, s, w);
+  __device__ static __forceinline__ void axis_weights(double s, double w[W]) {
+    w[0] = 1.0 - s;
+    w[1] = s;
+  }
+  __device__ static __forceinline__ void offsets(int k, int& ox, int& oy, int& oz) {
+    ox = k & 1;
+    oy = (k >> 1) & 1;
+    oz = (k >> 2) & 1;
   }
 };
 
 template <>
 struct Stencil<1> {
   static constexpr int kSites = 27, kLanes = 32;
-  __device__ static __forceinline__ void locate(const double X[3], const Geom& g, Cube& q) {
-    const int n3[3] = {g.nx, g.ny, g.nz};
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const double c = floor(X[d] + 0.5);
-      q.s[d] = X[d] - c;
-      q.base[d] = cell_of((int)c - 1, n3[d]);
-    }
+  static constexpr int W = 3;
+  __device__ static __forceinline__ int base_of(double x, int n, double& s) {
+    const double c = floor(x + 0.5);
+    s = x - c;
+    const int b = (int)c - 1;
+    return b < 0 ? b + n : b;  // (c = 0: the site below is the last one)
   }
-  __device__ static __forceinline__ void site(const Cube& q, const Geom& g, int k, int& cx,
-                                              int& cy, int& cz, int& s, double& w) {
-    const int ox = k % 3, oy = (k / 3) % 3, oz = k / 9;
-    cx = q.base[0] + ox;
-    cy = q.base[1] + oy;
-    cz = q.base[2] + oz;
-    cx = cx >= g.nx ? cx - g.nx : cx;
-    cy = cy >= g.ny ? cy - g.ny : cy;
-    cz = cz >= g.nz ? cz - g.nz : cz;
-    s = cx + g.nx * (cy + g.ny * cz);
-    w = kernel3(q.s[0] - (double)(ox - 1)) * kernel3(q.s[1] - (double)(oy - 1)) *
-        kernel3(q.s[2] - (double)(oz - 1));
+  __device__ static __forceinline__ void axis_weights(double s, double w[W]) {
+    const double q = sqrt(1.0 - 3.0 * s * s), a = 2.0 - q;
+    w[0] = (a - 3.0 * s) * (1.0 / 6.0);
+    w[1] = (1.0 + q) * (1.0 / 3.0);
+    w[2] = (a + 3.0 * s) * (1.0 / 6.0);
+  }
+  __device__ static __forceinline__ void offsets(int k, int& ox, int& oy, int& oz) {
+    ox = k % 3;
+    oy = (k / 3) % 3;
+    oz = k / 9;
   }
 };
+
+template <int ST>
+__device__ __forceinline__ void locate(const double X[3], const Geom& g, Cube& q) {
+  const int n3[3] = {g.nx, g.ny, g.nz};
+  bool in = true;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    q.base[d] = Stencil<ST>::base_of(X[d], n3[d], q.s[d]);
+    in = in & ((unsigned)q.base[d] < (unsigned)n3[d]);
+  }
+  if (!in) {  // (positions are wrapped: only at bound ones outside the box)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) q.base[d] = cell_of(q.base[d], n3[d]);
+  }
+}
+
+// Site k of the stencil with lowest site q.base.
+template <int ST>
+__device__ __forceinline__ void stencil_site(const Cube& q, const Geom& g, int k, int& cx, int& cy,
+                                             int& cz, int& site) {
+  int ox, oy, oz;
+  Stencil<ST>::offsets(k, ox, oy, oz);
+  cx = q.base[0] + ox;
+  cy = q.base[1] + oy;
+  cz = q.base[2] + oz;
+  cx = cx >= g.nx ? cx - g.nx : cx;
+  cy = cy >= g.ny ? cy - g.ny : cy;
+  cz = cz >= g.nz ? cz - g.nz : cz;
+  site = cx + g.nx * (cy + g.ny * cz);
+}
+
+// The sites of a stencil axis by axis: off[d][o] is what site o of axis d
+// adds to the site index (x, nx y, nx ny z) and w[d][o] its weight, so that a
+// site costs two additions and two products.
+template <int ST>
+struct StencilAxes {
+  int off[3][Stencil<ST>::W];
+  double w[3][Stencil<ST>::W];
+};
+
+template <int ST>
+__device__ __forceinline__ void stencil_axes(const Cube& q, const Geom& g, StencilAxes<ST>& ax) {
+  constexpr int W = Stencil<ST>::W;
+  const int n3[3] = {g.nx, g.ny, g.nz}, unit[3] = {1, g.nx, g.A};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    Stencil<ST>::axis_weights(q.s[d], ax.w[d]);
+    const int first = q.base[d] * unit[d], period = n3[d] * unit[d];
+#pragma unroll
+    for (int o = 0; o < W; ++o) {
+      const int f = first + o * unit[d];
+      ax.off[d][o] = f >= period ? f - period : f;
+    }
+  }
+}
+
+// v[o] by selects (an index known only at run time would put v in scratch).
+template <typename U>
+__device__ __forceinline__ U pick(const U (&v)[2], int o) {
+  const U a = v[0], b = v[1];
+  return o == 0 ? a : b;
+}
+template <typename U>
+__device__ __forceinline__ U pick(const U (&v)[3], int o) {
+  const U a = v[0], b = v[1], c = v[2];
+  const U ab = o == 0 ? a : b;
+  return o == 2 ? c : ab;
+}
+
+// The weights' squared sum over the stencil: the product of the axes' sums.
+template <int ST>
+__device__ __forceinline__ double squared_weights(const StencilAxes<ST>& ax) {
+  double S = 1.0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double a = 0.0;
+#pragma unroll
+    for (int o = 0; o < Stencil<ST>::W; ++o) a += ax.w[d][o] * ax.w[d][o];
+    S *= a;
+  }
+  return S;
+}
 
 }  // namespace lbmd_impl
