@@ -267,10 +267,11 @@ const char *lbmd_strerror(int code);
 
 /*
  * Captured cycles.  Runs ncycles coupled cycles (n_sub md_couple_substep()
- * steps and one lb_step() each, the schedule of Sec. 3 / Fig. 2) by replaying
- * one HIP graph of the cycle on the context's stream; identical in effect to
- * the step-by-step calls.  The graph is captured on first use and again after
- * lbmd_bind_particles() or lbmd_autotune().  Must start at an LB-step
+ * steps and one lb_step() each, the schedule of Sec. 3 / Fig. 2) on the
+ * context's stream; identical in effect to the step-by-step calls.  Cycles of
+ * many kernels are replayed from HIP graphs of one cycle, captured after the
+ * first few and again after lbmd_bind_particles() or lbmd_autotune(); short
+ * cycles are launched kernel by kernel.  Must start at an LB-step
  * boundary (LBMD_ESTATE otherwise).  Asynchronous.
  */
 int lbmd_run_cycles(lbmd *c, int32_t ncycles);

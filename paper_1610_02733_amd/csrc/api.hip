@@ -16,8 +16,10 @@ using namespace lbmd_impl;
 
 struct lbmd : Context {
   hipStream_t capture_stream = nullptr;
-  hipGraph_t graph_def = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
+  // one captured cycle per clock entry
+  hipGraph_t graph_def[2] = {nullptr, nullptr};
+  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+  int direct_cycles = 0;  // cycles launched kernel by kernel since the last drop_graph
 };
 
 namespace {
@@ -110,7 +112,7 @@ Plan make_plan(const lbmd_params* p, int32_t R) {
   L.item_rep = o; o = up(o + (size_t)(R + 1) * 4);
   L.part_rep = o; o = up(o + N * 4);
   L.pid = o; o = up(o + N * 4);
-  L.clock = o; o = up(o + sizeof(Clock));
+  L.clock = o; o = up(o + 2 * sizeof(Clock));
   L.fcons = o; o = up(o + 3 * N * 8);
   L.sort_x = o; o = up(o + 3 * N * 8);
   L.sort_v = o; o = up(o + 3 * N * 8);
@@ -290,17 +292,20 @@ hipError_t upload_tables(Context* c) {
 
 hipError_t write_clock(Context* c) {
   Clock clk{(long long)c->t_lb, (long long)(c->t_md - c->subs), c->cur, 0};
-  hipError_t e = hipMemcpyAsync(at(c, c->plan.lay.clock), &clk, sizeof(clk), hipMemcpyHostToDevice,
+  hipError_t e = hipMemcpyAsync(clock_of(c, c->clk), &clk, sizeof(clk), hipMemcpyHostToDevice,
                                 c->stream);
   if (e != hipSuccess) return e;
   return hipStreamSynchronize(c->stream);
 }
 
 void drop_graph(lbmd* c) {
-  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
-  if (c->graph_def) (void)hipGraphDestroy(c->graph_def);
-  c->graph_exec = nullptr;
-  c->graph_def = nullptr;
+  for (int k = 0; k < 2; ++k) {
+    if (c->graph_exec[k]) (void)hipGraphExecDestroy(c->graph_exec[k]);
+    if (c->graph_def[k]) (void)hipGraphDestroy(c->graph_def[k]);
+    c->graph_exec[k] = nullptr;
+    c->graph_def[k] = nullptr;
+  }
+  c->direct_cycles = 0;
 }
 
 // No particle has changed stencils at the current MD step count and no
@@ -337,6 +342,7 @@ int create(const lbmd_params* p, int32_t R, void* d_ws, size_t ws_bytes, void* h
   c->t_lb = c->t_md = 0;
   c->subs = 0;
   c->cur = 0;
+  c->clk = 0;
   c->sticky = LBMD_OK;
   c->tune.lb_blocks = 0;
   c->tune.part_blocks = 0;
@@ -373,6 +379,29 @@ hipError_t substep_launches(Context* c, int substep) {
   hipError_t e = launch_couple(c, substep);
   if (e == hipSuccess && c->plan.any_forces2) e = launch_forces_and_kick(c, substep);
   return e;
+}
+
+// Whether the caller is capturing the context's stream in a graph.
+bool being_captured(hipStream_t stream) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return s == hipStreamCaptureStatusActive;
+}
+
+// One LB step after md_steps MD steps; the device clock (in place for a
+// caller's own capture, see launch_clock_advance) and the host's copies of the
+// buffer and clock entry in use.
+hipError_t lb_step_launches(Context* c, int md_steps, bool in_place) {
+  hipError_t e =
+      launch_collide_stream(c, in_place ? nullptr : clock_of(c, 1 - c->clk), md_steps);
+  if (e == hipSuccess && in_place) e = launch_clock_advance(c, md_steps);
+  if (e != hipSuccess) return e;
+  c->cur = 1 - c->cur;
+  if (!in_place) c->clk = 1 - c->clk;
+  return hipSuccess;
 }
 
 // The n MD steps of an LB interval from its start.
@@ -462,13 +491,43 @@ int lb_step(lbmd* c) {
   if (!c) return LBMD_EINVAL;
   if (c->sticky) return c->sticky;
   if (c->plan.Ntot > 0 && c->subs != c->plan.n_sub) return LBMD_ESTATE;
-  int rc = fail(c, launch_collide_stream(c));
-  if (!rc) rc = fail(c, launch_clock_advance(c));
+  const int rc = fail(c, lb_step_launches(c, c->subs, being_captured(c->stream)));
   if (rc) return rc;
-  c->cur = 1 - c->cur;
   c->t_lb += 1;
   c->subs = 0;
   return LBMD_OK;
+}
+
+// Kernels of a cycle of n MD steps, and the numbers up to which it is launched
+// kernel by kernel.
+static int cycle_launches(const lbmd* c, int n) { return n > 0 ? 2 * n + 2 : 1; }
+constexpr int kDirectKernels = 6, kDirectCycles = 8;
+
+// Captures one cycle (n MD steps + one LB step) that starts from the current
+// clock entry, on a private stream; the kernels read the step clock from
+// device memory, so the graph serves every such cycle.
+static int capture_cycle(lbmd* c, int n) {
+  if (!c->capture_stream) {
+    int rc = fail(c, hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
+    if (rc) return rc;
+  }
+  hipStream_t user = c->stream;
+  const int k = c->clk, cur = c->cur;
+  c->stream = c->capture_stream;
+  hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
+  if (e == hipSuccess) e = interval_launches(c, n);
+  if (e == hipSuccess) e = lb_step_launches(c, n, false);
+  hipGraph_t g = nullptr;
+  const hipError_t e2 = hipStreamEndCapture(c->stream, &g);
+  c->stream = user;
+  c->clk = k;
+  c->cur = cur;
+  if (e == hipSuccess) e = e2;
+  if (e == hipSuccess) e = hipGraphInstantiate(&c->graph_exec[k], g, nullptr, nullptr, 0);
+  c->graph_def[k] = g;
+  const int rc = fail(c, e);
+  if (rc) drop_graph(c);
+  return rc;
 }
 
 int lbmd_run_cycles(lbmd* c, int32_t ncycles) {
@@ -478,42 +537,34 @@ int lbmd_run_cycles(lbmd* c, int32_t ncycles) {
   if (c->plan.Ntot > 0 && !c->bound) return LBMD_ESTATE;
   if (ncycles == 0) return LBMD_OK;
   const int n = c->plan.Ntot > 0 ? c->plan.n_sub : 0;
-  if (!c->graph_exec) {
-    // capture one cycle (n MD steps + one LB step) on a private stream; the
-    // kernels read the step clock from device memory, so the same graph
-    // serves every cycle
-    if (!c->capture_stream) {
-      int rc = fail(c, hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
-      if (rc) return rc;
-    }
-    hipStream_t user = c->stream;
-    c->stream = c->capture_stream;
-    hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
-    const int32_t saved_subs = c->subs;
-    if (e == hipSuccess) e = interval_launches(c, n);
-    c->subs = n;  // MD steps the clock advance accounts for
-    if (e == hipSuccess) e = launch_collide_stream(c);
-    if (e == hipSuccess) e = launch_clock_advance(c);
-    c->subs = saved_subs;
-    hipGraph_t g = nullptr;
-    const hipError_t e2 = hipStreamEndCapture(c->stream, &g);
-    c->stream = user;
-    if (e == hipSuccess) e = e2;
-    if (e == hipSuccess) e = hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0);
-    c->graph_def = g;
-    int rc = fail(c, e);
-    if (rc) {
-      drop_graph(c);
-      return rc;
-    }
-  }
+  // Launching a cycle kernel by kernel costs the host 2.6 to 3.5 us a kernel,
+  // replaying its graph 15 us and more for long ones (23 us for 12 kernels, 38
+  // for 42), after 65 to 165 us to capture it: a 50 x 41 x 37 fluid took 16.0
+  // us a cycle by graph and takes 6.1 by launches, 16^3 with n = 20 166 us by
+  // launches and 140 by graph.  So cycles of up to kDirectKernels kernels are
+  // always launched, longer ones for the first kDirectCycles (three cycles of
+  // the 128^3 polymer from a new state: 1271 -> 811 us).
+  const int kernels = cycle_launches(c, n);
+  const bool captured = being_captured(c->stream);
   for (int32_t k = 0; k < ncycles; ++k) {
-    int rc = fail(c, hipGraphLaunch(c->graph_exec, c->stream));
+    int rc = LBMD_OK;
+    hipGraphExec_t& exec = c->graph_exec[c->clk];
+    if (kernels <= kDirectKernels || captured || (!exec && c->direct_cycles < kDirectCycles)) {
+      rc = fail(c, interval_launches(c, n));
+      if (!rc) rc = fail(c, lb_step_launches(c, n, captured));
+      c->direct_cycles += captured ? 0 : 1;
+    } else {
+      if (!exec) rc = capture_cycle(c, n);
+      if (!rc) rc = fail(c, hipGraphLaunch(exec, c->stream));
+      if (!rc) {
+        c->cur = 1 - c->cur;
+        c->clk = 1 - c->clk;
+      }
+    }
     if (rc) return rc;
+    c->t_lb += 1;
+    c->t_md += n;
   }
-  c->t_lb += ncycles;
-  c->t_md += (int64_t)ncycles * n;
-  if (ncycles & 1) c->cur = 1 - c->cur;
   return LBMD_OK;
 }
 
@@ -880,11 +931,7 @@ int lbmd_adjoint_record(lbmd* c, const void* d_state, int32_t ncycles) {
     a.t_lb[j] = c->t_lb;
     a.t_md[j] = c->t_md;
     e = interval_launches(c, n);
-    c->subs = n;
-    if (e == hipSuccess) e = launch_collide_stream(c);
-    if (e == hipSuccess) e = launch_clock_advance(c);
-    c->subs = 0;
-    c->cur = 1 - c->cur;
+    if (e == hipSuccess) e = lb_step_launches(c, n, false);
     c->t_lb += 1;
     c->t_md += n;
   }
@@ -1088,7 +1135,7 @@ int lbmd_autotune(lbmd* c, const char* cache_path, int32_t* out_lb_blocks,
     int best_lb = 0;
     for (int q : lb_cand) {
       c->tune.lb_blocks = q;
-      const double ms = time_ms(c, [&] { return launch_collide_stream(c); }, 3, &e);
+      const double ms = time_ms(c, [&] { return launch_collide_stream(c, nullptr, 0); }, 3, &e);
       if (e != hipSuccess) return fail(c, e);
       if (ms < best) {
         best = ms;

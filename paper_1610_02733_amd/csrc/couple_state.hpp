@@ -540,7 +540,7 @@ inline CoupleArgs<T> couple_args(Context* c, int substep) {
   a.md = (const RepMD*)at(c, L.rep_md);
   a.part_rep = (const int32_t*)at(c, L.part_rep);
   a.pid = (const int32_t*)at(c, L.pid);
-  a.clock = (const Clock*)at(c, L.clock);
+  a.clock = clock_of(c, c->clk);
   a.rec = c->rec_part ? c->rec_part + (size_t)substep * kAdjRec * (size_t)c->plan.Ntot : nullptr;
   a.lsite = (int32_t*)at(c, L.slist_site);
   a.ldelta = (Vec4<T>*)at(c, L.slist_delta);

@@ -385,7 +385,7 @@ static hipError_t launch_binning(Context* c, int pos_step) {
                      c->stream, count, nc);
   hipLaunchKernelGGL(k_bin_count, dim3((unsigned)((N + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                      c->stream, (const double*)c->x, N, (const RepMD*)at(c, L.rep_md),
-                     (const int32_t*)at(c, L.part_rep), (const Clock*)at(c, L.clock), pos_step,
+                     (const int32_t*)at(c, L.part_rep), (const Clock*)clock_of(c, c->clk), pos_step,
                      C, c->plan.cell_cap, count, (int32_t*)at(c, L.bin_of),
                      (int32_t*)at(c, L.bin_slot), (int32_t*)at(c, L.bin_ovf));
   return hipGetLastError();

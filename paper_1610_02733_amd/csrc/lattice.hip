@@ -63,6 +63,8 @@ struct StreamArgs {
   const RepLB<T>* __restrict__ rep;
   const int32_t* __restrict__ item_off;
   const Clock* __restrict__ clock;
+  Clock* __restrict__ next;  // the step's advanced clock goes here (null: nowhere)
+  int md_steps;              // MD steps of the interval the step ends
   Vec4<T>* __restrict__ jrec;                 // recording: J consumed at marked sites
   unsigned long long* __restrict__ mrec;      // recording: mark words
   int R, nitems;
@@ -283,6 +285,8 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
       if ((gsite & 63) == 0 && word) a.mark[gsite >> 6] = 0ull;
     }
   }
+  if (a.next && blockIdx.x == 0 && threadIdx.x == 0)
+    *a.next = Clock{t + 1, a.clock->t_md + a.md_steps, 1 - cur, 0};
 }
 
 template <typename T>
@@ -296,7 +300,9 @@ static StreamArgs<T> stream_args(Context* c) {
   a.mark = (unsigned long long*)at(c, c->plan.lay.mark);
   a.rep = (const RepLB<T>*)at(c, c->plan.lay.rep_lb);
   a.item_off = (const int32_t*)at(c, c->plan.lay.item_rep);
-  a.clock = (const Clock*)at(c, c->plan.lay.clock);
+  a.clock = clock_of(c, c->clk);
+  a.next = nullptr;
+  a.md_steps = 0;
   a.R = c->plan.R;
   a.nitems = c->plan.nitems;
   a.varc = c->p[0].variant == 3 ? 1 : 0;
@@ -317,8 +323,10 @@ static void collide_stream_mode(Context* c, const StreamArgs<T>& a, int blocks) 
 }
 
 template <typename T>
-static hipError_t collide_stream_t(Context* c) {
+static hipError_t collide_stream_t(Context* c, Clock* next, int md_steps) {
   StreamArgs<T> a = stream_args<T>(c);
+  a.next = next;
+  a.md_steps = md_steps;
   const int blocks = c->tune.lb_blocks > 0 ? std::min(c->tune.lb_blocks, a.nitems) : a.nitems;
   // the row path's kernel is instantiated on its own when no replica needs
   // the general one (fewer registers, more waves in flight)
@@ -331,11 +339,14 @@ static hipError_t collide_stream_t(Context* c) {
   return hipGetLastError();
 }
 
-hipError_t launch_collide_stream(Context* c) {
-  return c->plan.prec == 32 ? collide_stream_t<float>(c) : collide_stream_t<double>(c);
+hipError_t launch_collide_stream(Context* c, Clock* next, int md_steps) {
+  return c->plan.prec == 32 ? collide_stream_t<float>(c, next, md_steps)
+                            : collide_stream_t<double>(c, next, md_steps);
 }
 
-// End of an LB step: advance the device clock (graph-capturable).
+// The clock advanced in place, after an LB step that did not write the other
+// entry: a caller captures the step in a graph of its own, which then replays
+// from whatever step the entry holds.
 __global__ void k_clock_advance(Clock* __restrict__ clk, int md_steps) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     clk->t_lb += 1;
@@ -344,9 +355,9 @@ __global__ void k_clock_advance(Clock* __restrict__ clk, int md_steps) {
   }
 }
 
-hipError_t launch_clock_advance(Context* c) {
-  hipLaunchKernelGGL(k_clock_advance, dim3(1), dim3(64), 0, c->stream,
-                     (Clock*)at(c, c->plan.lay.clock), (int)c->subs);
+hipError_t launch_clock_advance(Context* c, int md_steps) {
+  hipLaunchKernelGGL(k_clock_advance, dim3(1), dim3(64), 0, c->stream, clock_of(c, c->clk),
+                     md_steps);
   return hipGetLastError();
 }
 

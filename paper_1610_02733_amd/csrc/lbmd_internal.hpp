@@ -64,7 +64,10 @@ struct RepMD {
 };
 
 // Device step clock: read by the kernels so that a captured cycle replays
-// unchanged; advanced by a one-thread kernel at the end of each LB step.
+// unchanged.  Two entries: every kernel of a cycle reads the entry the host
+// names (Context::clk) and the LB step writes the next cycle's values into the
+// other one, which no kernel in flight reads, so that advancing takes no launch
+// of its own (about 4 us a cycle, as much as the step of a small lattice).
 struct Clock {
   long long t_lb;  // LB steps done
   long long t_md;  // MD steps done at the start of the current LB interval
@@ -86,7 +89,7 @@ struct Layout {
   size_t part_rep;   // [Ntot] int32: replica of each particle
   size_t pid;        // [Ntot] int32: replica-local identity of the particle in each slot
                      // (its index at binding; the particle noise counter follows it)
-  size_t clock;      // Clock
+  size_t clock;      // Clock[2]
   size_t fcons;      // [3][Ntot] double: conservative force at the current positions
   size_t sort_x;     // [3][Ntot] double: particle sort scratch (positions)
   size_t sort_v;     // [3][Ntot] double: particle sort scratch (velocities)
@@ -201,6 +204,7 @@ struct Context {
   int64_t t_lb, t_md;
   int32_t subs;
   int cur;  // population buffer holding the current state (mirrors Clock::cur)
+  int clk;  // clock entry of the current cycle
   int sticky;
   Tune tune;
   bool graph_ok;
@@ -208,6 +212,9 @@ struct Context {
 };
 
 inline void* at(const Context* c, size_t off) { return c->ws + off; }
+inline Clock* clock_of(const Context* c, int entry) {
+  return (Clock*)at(c, c->plan.lay.clock) + entry;
+}
 
 // Copy of a per-replica table entry that the whole block reads, through the
 // constant address space so that it is fetched with scalar loads into
@@ -227,12 +234,12 @@ __device__ __forceinline__ U scalar_copy(const U* p) {
 }
 
 // Launchers (return hipError_t of the launch).
-hipError_t launch_collide_stream(Context* c);
+hipError_t launch_collide_stream(Context* c, Clock* next, int md_steps);
 hipError_t launch_collide_stream_adjoint(Context* c);
 hipError_t launch_couple_adjoint(Context* c);
 hipError_t launch_adjoint_fold(Context* c);
 hipError_t launch_store_counters(Context* c, void* dst, int64_t t_lb, int64_t t_md);
-hipError_t launch_clock_advance(Context* c);
+hipError_t launch_clock_advance(Context* c, int md_steps);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 size_t sort_temp_bytes(int64_t N);
 hipError_t launch_sort_particles(Context* c, int32_t* d_perm, bool* too_small);
