@@ -404,8 +404,10 @@ hipError_t lb_step_launches(Context* c, int md_steps, bool in_place) {
   return hipSuccess;
 }
 
-// The n MD steps of an LB interval from its start.
+// The n MD steps of an LB interval from its start, as one launch where the
+// replicas are small enough.
 hipError_t interval_launches(Context* c, int n) {
+  if (n > 0 && interval_in_one(c)) return launch_interval(c);
   hipError_t e = hipSuccess;
   for (int s = 0; s < n && e == hipSuccess; ++s) e = substep_launches(c, s);
   return e;
@@ -500,7 +502,9 @@ int lb_step(lbmd* c) {
 
 // Kernels of a cycle of n MD steps, and the numbers up to which it is launched
 // kernel by kernel.
-static int cycle_launches(const lbmd* c, int n) { return n > 0 ? 2 * n + 2 : 1; }
+static int cycle_launches(const lbmd* c, int n) {
+  return n == 0 ? 1 : (interval_in_one(c) ? 3 : 2 * n + 2);
+}
 constexpr int kDirectKernels = 6, kDirectCycles = 8;
 
 // Captures one cycle (n MD steps + one LB step) that starts from the current

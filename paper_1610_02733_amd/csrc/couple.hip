@@ -550,6 +550,56 @@ __global__ __launch_bounds__(kBlock) void k_couple(CoupleArgs<T> a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// A whole LB interval of a small replica in one workgroup (launch_interval):
+// per MD step the coupling (couple_lane) and, after a barrier, the step's
+// after-step work, with no launch in between.  A replica's particles meet only
+// each other, so workgroup barriers order the steps, and the replicas of a
+// batch run side by side.  Small systems are bound by launches, two a step,
+// each a chain of loads and dependent arithmetic; here the chain is all, until
+// one CU's issue rate takes over: 41 -> 24.6 us a cycle of five MD steps with 8
+// particles in 24^3, 47 -> 33 with 32, 52 -> 40 with 128, 57 -> 53 with 256, and
+// 61 -> 71 with 384.
+// Few: the least particles, whose chain is shortest with one corner per lane
+// and the corner-cache refill in the same launch (24.6 against 28.0 us with 8
+// particles; with 64 the refill is better left to the whole chip, 35.6 against
+// 45.1 us).
+// ---------------------------------------------------------------------------
+template <typename T, bool Rec, bool Few>
+__global__ __launch_bounds__(512) void k_interval(CoupleArgs<T> a, int n_sub) {
+  constexpr int L = Few ? 8 : DirectShape<0>::kLanes;
+  __shared__ int s_l, s_m;
+  const int rr = blockIdx.x;
+  const RepMD m = scalar_copy(a.md + rr);
+  const int64_t lanes = (int64_t)m.N * L;
+  if (lanes == 0) return;
+  const unsigned long long t0 = (unsigned long long)a.clock->t_md;
+  if (Few) {
+    const T* __restrict__ pop = a.pop[a.clock->cur];
+    for (int64_t t = threadIdx.x; t < (int64_t)m.N * kRefillLanes; t += blockDim.x)
+      refill_particle<true>(a, m, pop, m.part_off + t / kRefillLanes);
+  }
+  const int64_t entry0 = (int64_t)m.part_off * 8, mover0 = m.part_off;
+  for (int s = 0; s < n_sub; ++s) {
+    if (threadIdx.x == 0) s_l = s_m = 0;
+    __syncthreads();
+    const StepFlags st{s == 0, s == n_sub - 1, s == n_sub - 1};
+    const StepLists lists{entry0, mover0, &s_l, &s_m};
+    double* rec = Rec ? a.rec + (size_t)s * kAdjRec * (size_t)a.N : nullptr;
+    for (uint32_t t = threadIdx.x; t < (uint32_t)lanes; t += blockDim.x)
+      couple_lane<T, Rec, 0, L, false, false, true>(a, m, rr, m.part_off, t, (uint32_t)lanes,
+                                                    t0 + s, st, lists, rec);
+    __syncthreads();
+    const int nl = s_l, nm = s_m;
+    after_step_lists<true, T>(a, entry0, nl, SiteTable<T>{nullptr, nullptr}, false, 0,
+                              Vec4<T>{T(0), T(0), T(0), T(0)});
+    after_step_movers<T, 0, true, true, true>(a, m,
+                                              reinterpret_cast<const int4*>(a.mlist) + mover0, nm,
+                                              (long long)(t0 + s), make_int4(0, 0, 0, 0));
+    __syncthreads();
+  }
+}
+
 // After an MD step without a force kernel: the after-step work
 // (after_step_item) as a launch of its own.
 // With Reduce, the shared-site transfers of each segment are summed per site
@@ -686,6 +736,52 @@ static hipError_t couple_t(Context* c, int substep) {
 hipError_t launch_couple(Context* c, int substep) {
   if (c->plan.Ntot == 0) return hipSuccess;
   return c->plan.prec == 32 ? couple_t<float>(c, substep) : couple_t<double>(c, substep);
+}
+
+// Whether the MD steps of an LB interval run as one launch, a workgroup per
+// replica (k_interval): the trilinear stencil, no position-dependent forces,
+// and no replica of more than kIntervalMax particles, about where one CU takes
+// as long as the launches (FP32 47 against 55 us a cycle with 200 particles, 53
+// against 57 with 256; FP64 55 against 60 and 62 against 63).
+constexpr int kIntervalMax = 224;
+constexpr int kIntervalFew = 16;
+
+static int largest_replica(const Context* c) {
+  int n = 0;
+  for (const lbmd_params& p : c->p) n = std::max(n, (int)p.n_particles);
+  return n;
+}
+
+bool interval_in_one(const Context* c) {
+  return c->plan.Ntot > 0 && !c->plan.any_forces2 && c->p[0].stencil == 0 &&
+         largest_replica(c) <= kIntervalMax;
+}
+
+template <typename T, bool Rec>
+static hipError_t interval_t(Context* c) {
+  const CoupleArgs<T> a = couple_args<T>(c, 0);
+  const int n = largest_replica(c);
+  const bool few = n <= kIntervalFew;
+  if (!few) {
+    const hipError_t e = launch_refill_st<T, 0>(c, a);
+    if (e != hipSuccess) return e;
+  }
+  const int lanes = n * (few ? kRefillLanes : DirectShape<0>::kLanes);
+  const dim3 grid((unsigned)c->plan.R), block(std::min(512, (lanes + 63) / 64 * 64));
+  if (few)
+    hipLaunchKernelGGL((k_interval<T, Rec, true>), grid, block, 0, c->stream, a, c->plan.n_sub);
+  else
+    hipLaunchKernelGGL((k_interval<T, Rec, false>), grid, block, 0, c->stream, a, c->plan.n_sub);
+  c->cache_dirty = false;
+  c->retag = false;
+  return hipGetLastError();
+}
+
+// All MD steps of an LB interval (interval_in_one), from an LB-step boundary.
+hipError_t launch_interval(Context* c) {
+  if (c->rec_part)
+    return c->plan.prec == 32 ? interval_t<float, true>(c) : interval_t<double, true>(c);
+  return c->plan.prec == 32 ? interval_t<float, false>(c) : interval_t<double, false>(c);
 }
 
 // ---------------------------------------------------------------------------

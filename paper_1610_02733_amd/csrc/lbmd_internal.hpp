@@ -250,6 +250,8 @@ hipError_t launch_get_populations(Context* c, int rep, void* dst);
 hipError_t launch_set_populations(Context* c, int rep, const void* src);
 hipError_t launch_get_transfer(Context* c, int rep, void* dst);
 hipError_t launch_couple(Context* c, int substep);
+bool interval_in_one(const Context* c);
+hipError_t launch_interval(Context* c);
 hipError_t launch_couple_refill_only(Context* c);
 hipError_t launch_init_forces(Context* c);
 hipError_t launch_init_pid(Context* c);
