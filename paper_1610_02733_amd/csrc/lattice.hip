@@ -68,6 +68,7 @@ struct StreamArgs {
   Vec4<T>* __restrict__ jrec;                 // recording: J consumed at marked sites
   unsigned long long* __restrict__ mrec;      // recording: mark words
   int R, nitems;
+  int reverse;  // items in reverse order every other step (keep_stores)
   int varc;  // variant 3: J belongs to the fluid state (fields read j + J)
 };
 
@@ -196,12 +197,26 @@ __device__ __forceinline__ int xcd_first_item() {
   return xcd * q8 + (xcd < r8 ? xcd : r8) + blockIdx.x / 8;
 }
 
+// Stores 19 values, plane i at o + i A: through the caches, or streamed past
+// them (keep_stores; a template argument, since a branch's two sides differ in
+// nothing but the hint, which the compiler then drops).
+template <bool Cached, typename T>
+__device__ __forceinline__ void store_planes(T* __restrict__ o, size_t A, const T d[19]) {
+  if constexpr (Cached) {
+#pragma unroll
+    for (int i = 0; i < 19; ++i) o[(size_t)i * A] = d[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 19; ++i) __builtin_nontemporal_store(d[i], o + (size_t)i * A);
+  }
+}
+
 // With Rec, the transfer field and the mark words the step consumes are also
 // copied out for the reverse sweep (the adjoint needs the force density of
 // the step and the set of sites the MD steps touched).
 // Mode: 0 every replica takes the general path, 1 every replica the row
 // path, 2 per replica (a batch mixing both).
-template <typename T, bool Rec, bool VarC, int Mode>
+template <typename T, bool Rec, bool VarC, int Mode, bool Cached>
 __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
   __shared__ RowEdges<T> edge;
   const int cur = a.clock->cur;
@@ -216,7 +231,8 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
   // sites per edge: reads 1.20x -> 1.03x the algorithmic bytes).  The row path
   // reads aligned runs and keeps the plain order.
   const int item0 = Mode == 0 ? xcd_first_item() : (int)blockIdx.x;
-  for (int item = item0; item < a.nitems; item += gridDim.x) {
+  for (int it = item0; it < a.nitems; it += gridDim.x) {
+    const int item = a.reverse && cur ? a.nitems - 1 - it : it;
     // the replica is uniform across the block: keep its constants in scalar
     // registers
     const int rr = __builtin_amdgcn_readfirstlane(
@@ -269,24 +285,39 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream(StreamArgs<T> a) {
         hw[4] = o1.w0; hw[5] = o1.w1; hw[6] = o1.w2; hw[7] = o1.w3;
       }
       collide_deviation<T, VarC>(d, Fx, Fy, Fz, hw, q.k, Jx, Jy, Jz);
-      // every population is written once per step: stream the stores past the
-      // caches (non-temporal hint)
       T* __restrict__ o = dst + 19 * (size_t)q.site_off;
-      if (rows || off32) {
-        const uint32_t own = ((uint32_t)z * 19u) * (uint32_t)q.g.A + (uint32_t)(y * q.g.nx + x);
-#pragma unroll
-        for (int i = 0; i < 19; ++i)
-          __builtin_nontemporal_store(d[i], o + (size_t)i * q.g.A + own);
-      } else {
-        const size_t own = pop_offset(q.g, 0, x, y, z);
-#pragma unroll
-        for (int i = 0; i < 19; ++i) __builtin_nontemporal_store(d[i], o + own + (size_t)i * q.g.A);
-      }
+      if (rows || off32)
+        store_planes<Cached>(
+            o + (((uint32_t)z * 19u) * (uint32_t)q.g.A + (uint32_t)(y * q.g.nx + x)),
+            (size_t)q.g.A, d);
+      else
+        store_planes<Cached>(o + pop_offset(q.g, 0, x, y, z), (size_t)q.g.A, d);
       if ((gsite & 63) == 0 && word) a.mark[gsite >> 6] = 0ull;
     }
   }
   if (a.next && blockIdx.x == 0 && threadIdx.x == 0)
     *a.next = Clock{t + 1, a.clock->t_md + a.md_steps, 1 - cur, 0};
+}
+
+// Cache hints of the population stores, by the size of a population buffer
+// against the 256 MB memory-side cache (and the 32 MB of L2 below it).  A
+// lattice that is far larger streams past the caches (non-temporal stores).
+// One whose step fits in them keeps what it writes, which the next step reads;
+// with aligned rows and up to twice that size, every other step also takes its
+// items in reverse, so that it starts with the part written last.  Measured,
+// streamed against kept, us a step: general path 60^3 (16 MB) 7.2/7.8, 66^3
+// (22 MB) 12.3/9.7, 96^3 (67 MB) 28.0/21.4, 121 x 120 x 119 (131 MB) 56.0/39.1,
+// 126^3 (152 MB) 64.8/61.4, 132^3 (175 MB) 67.8/71.7, 144^3 (227 MB) 82.9/84.8;
+// row path 64 x 64 x 128 (40 MB) 15.6/16.1, 128 x 128 x 64 (80 MB) 29.2/27.3,
+// 128^3 (159 MB) 54.0/50.4, 256 x 128 x 128 (319 MB) 103.8/96.5 (109.8 without
+// the reversal), 256 x 256 x 96 (478 MB) 155/150, 256 x 256 x 128 (637 MB)
+// 204.6/207.7, 256^3 406.8/419.5.  With particles, whose kernels run between
+// the steps, the row path gains nothing from keeping its stores (128^3 polymer,
+// three cycles and a copy, 794/799).
+static bool keep_stores(const Plan& pl) {
+  const double mb = 19.0 * (double)pl.P * (pl.prec == 32 ? 4.0 : 8.0) / 1e6;
+  if (pl.row_replicas == pl.R) return pl.Ntot == 0 && mb > 60.0 && mb < 520.0;
+  return pl.row_replicas == 0 && mb > 20.0 && mb < 160.0;
 }
 
 template <typename T>
@@ -306,19 +337,21 @@ static StreamArgs<T> stream_args(Context* c) {
   a.R = c->plan.R;
   a.nitems = c->plan.nitems;
   a.varc = c->p[0].variant == 3 ? 1 : 0;
+  a.reverse = c->plan.row_replicas == c->plan.R && keep_stores(c->plan) ? 1 : 0;
   return a;
 }
 
-template <typename T, int Mode>
+template <typename T, int Mode, bool Cached>
 static void collide_stream_mode(Context* c, const StreamArgs<T>& a, int blocks) {
+  const dim3 grid(blocks), block(kBlock);
   if (c->p[0].variant == 3)  // no adjoint for variant 3: never recording
-    hipLaunchKernelGGL((k_collide_stream<T, false, true, Mode>), dim3(blocks), dim3(kBlock), 0,
-                       c->stream, a);
+    hipLaunchKernelGGL((k_collide_stream<T, false, true, Mode, Cached>), grid, block, 0, c->stream,
+                       a);
   else if (a.jrec)
-    hipLaunchKernelGGL((k_collide_stream<T, true, false, Mode>), dim3(blocks), dim3(kBlock), 0,
-                       c->stream, a);
+    hipLaunchKernelGGL((k_collide_stream<T, true, false, Mode, Cached>), grid, block, 0, c->stream,
+                       a);
   else
-    hipLaunchKernelGGL((k_collide_stream<T, false, false, Mode>), dim3(blocks), dim3(kBlock), 0,
+    hipLaunchKernelGGL((k_collide_stream<T, false, false, Mode, Cached>), grid, block, 0,
                        c->stream, a);
 }
 
@@ -330,12 +363,17 @@ static hipError_t collide_stream_t(Context* c, Clock* next, int md_steps) {
   const int blocks = c->tune.lb_blocks > 0 ? std::min(c->tune.lb_blocks, a.nitems) : a.nitems;
   // the row path's kernel is instantiated on its own when no replica needs
   // the general one (fewer registers, more waves in flight)
-  if (c->plan.row_replicas == c->plan.R)
-    collide_stream_mode<T, 1>(c, a, blocks);
+  const bool rows = c->plan.row_replicas == c->plan.R, keep = keep_stores(c->plan);
+  if (rows && keep)
+    collide_stream_mode<T, 1, true>(c, a, blocks);
+  else if (rows)
+    collide_stream_mode<T, 1, false>(c, a, blocks);
+  else if (keep)
+    collide_stream_mode<T, 0, true>(c, a, blocks);
   else if (c->plan.row_replicas == 0)
-    collide_stream_mode<T, 0>(c, a, blocks);
+    collide_stream_mode<T, 0, false>(c, a, blocks);
   else
-    collide_stream_mode<T, 2>(c, a, blocks);
+    collide_stream_mode<T, 2, false>(c, a, blocks);
   return hipGetLastError();
 }
 
@@ -614,8 +652,8 @@ hipError_t launch_moments_rows(Context* c, void* d_rho, void* d_u, double* rows)
 // replica ([19][S] and [3][S] arrays in the run precision).
 // ---------------------------------------------------------------------------
 // Copy out: the populations pulled as in the collide-stream kernel (aligned
-// rows or 32-bit offsets) and stored past the caches, one 256-site item per
-// block.  Bound by memory, with the 19 separate output arrays as its limit:
+// rows or 32-bit offsets) and stored under the same cache hints, one 256-site
+// item per block.  Bound by memory, with the 19 separate output arrays as its limit:
 // 435 us at 256^3 in FP32 (5.9 TB/s; the collide-stream kernel, which writes
 // interleaved planes, 6.3), against 449 us with 64-bit gathers and cached
 // stores.
@@ -623,7 +661,7 @@ hipError_t launch_moments_rows(Context* c, void* d_rho, void* d_u, double* rows)
 // transfer the site has received in the current interval (J at marked
 // sites), so that it shows the populations as the paper's variant C holds
 // them after each MD step.
-template <typename T, int Mode>
+template <typename T, int Mode, bool Cached>
 __global__ __launch_bounds__(kBlock) void k_get_pop(const T* __restrict__ pop,
                                                     T* __restrict__ plain,
                                                     const Vec4<T>* __restrict__ pend,
@@ -661,9 +699,7 @@ __global__ __launch_bounds__(kBlock) void k_get_pop(const T* __restrict__ pop,
 #pragma unroll
     for (int i = 0; i < 19; ++i) d[i] += dd[i];
   }
-  const size_t S = (size_t)q.g.S;
-#pragma unroll
-  for (int i = 0; i < 19; ++i) __builtin_nontemporal_store(d[i], plain + (size_t)i * S + r);
+  store_planes<Cached>(plain + r, (size_t)q.g.S, d);
 }
 
 template <typename T>
@@ -718,12 +754,15 @@ static hipError_t copy_t(Context* c, int rep, void* plain, int what) {
   const Vec4<T>* pend = p.variant == 3 ? (const Vec4<T>*)at(c, c->plan.lay.transfer) : nullptr;
   const unsigned long long* mark = (const unsigned long long*)at(c, c->plan.lay.mark);
   const RepLB<T>* tab = (const RepLB<T>*)at(c, c->plan.lay.rep_lb);
+  const bool keep = keep_stores(c->plan);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, c->stream, (const T*)pop, (T*)plain,
+                       pend, mark, tab, rep);
+  };
   if (row_path(p))
-    hipLaunchKernelGGL((k_get_pop<T, 1>), dim3(blocks), dim3(kBlock), 0, c->stream, pop, (T*)plain,
-                       pend, mark, tab, rep);
+    keep ? go(k_get_pop<T, 1, true>) : go(k_get_pop<T, 1, false>);
   else
-    hipLaunchKernelGGL((k_get_pop<T, 0>), dim3(blocks), dim3(kBlock), 0, c->stream, pop, (T*)plain,
-                       pend, mark, tab, rep);
+    keep ? go(k_get_pop<T, 0, true>) : go(k_get_pop<T, 0, false>);
   return hipGetLastError();
 }
 

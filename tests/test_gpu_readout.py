@@ -79,3 +79,24 @@ def test_chunked_moments_of_a_batch(lb):
     for r, f in enumerate(fs):
         check_totals(lb, tot[r], f, 32)
         assert bool((B.populations(r) == f).all())
+
+
+@pytest.mark.parametrize("shape,other", [((128, 128, 64), (5, 4, 3)), ((66, 67, 65), (64, 3, 2)),
+                                         ((256, 128, 81), (5, 4, 3))])
+def test_kept_and_reversed_steps(lb, shape, other):
+    """Steps whose stores stay in the caches, with aligned rows in reverse item
+    order every other step, against the same system in a batch with a replica
+    of the other load path, where neither applies: same arithmetic per site
+    (five roundings a step of deviations up to 0.1 w_i rho0)."""
+    import torch
+    kw = dict(precision=32, kT=1e-4, seed=5, replica=0, body_force=(1e-4, 0.0, 0.0))
+    f = state(lb, shape, 32, 6)
+    a = lb.Lattice(shape, **kw)
+    a.set_populations(f)
+    b = lb.Batch([(shape, dict(kw, n_particles=0)), (other, dict(kw, replica=1, n_particles=0))])
+    assert lb.lib().lbmd_batch_set_populations(b._h, 0, ctypes.c_void_p(f.data_ptr())) == 0
+    a.run_cycles(5)
+    b.run_cycles(5)
+    w = torch.tensor(lb.WEIGHTS, dtype=torch.float64, device="cuda").reshape(19, 1)
+    d = (a.populations().double() - b.populations(0).double()).abs() / w
+    assert float(d.max()) < 25 * 0.1 * EPS[32]
