@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kBlock) void k_couple(CoupleArgs<T> a) {
 // ---------------------------------------------------------------------------
 template <typename T, bool Rec, bool Few>
 __global__ __launch_bounds__(512) void k_interval(CoupleArgs<T> a, int n_sub) {
-  constexpr int L = Few ? 8 : DirectShape<0>::kLanes;
+  constexpr int L = Few ? 8 : kIntervalLanes;
   __shared__ int s_l, s_m;
   const int rr = blockIdx.x;
   const RepMD m = scalar_copy(a.md + rr);
@@ -688,7 +688,7 @@ static hipError_t couple_st(Context* c, int substep) {
   // lanes per particle of the coupling kernel: eight while recording, else
   // the tuned count or the default
   const int L = a.rec ? 8 : (c->tune.couple_lanes > 0 ? c->tune.couple_lanes
-                                                        : DirectShape<ST>::kLanes);
+                                                        : default_lanes<ST>(N));
   const dim3 cgrid(grid_for((N * L + kBlock - 1) / kBlock, c->tune.part_blocks));
   // with position-dependent forces (never recorded) the kernel also bins
   const bool bin = c->plan.any_forces2 && !a.rec;
@@ -766,7 +766,7 @@ static hipError_t interval_t(Context* c) {
     const hipError_t e = launch_refill_st<T, 0>(c, a);
     if (e != hipSuccess) return e;
   }
-  const int lanes = n * (few ? kRefillLanes : DirectShape<0>::kLanes);
+  const int lanes = n * (few ? kRefillLanes : kIntervalLanes);
   const dim3 grid((unsigned)c->plan.R), block(std::min(512, (lanes + 63) / 64 * 64));
   if (few)
     hipLaunchKernelGGL((k_interval<T, Rec, true>), grid, block, 0, c->stream, a, c->plan.n_sub);

@@ -299,16 +299,22 @@ __device__ __forceinline__ Vec4<T> gather_site_moments(const T* __restrict__ pop
 // and items [nseg, 2 nseg) the transfers.  One block runs one item; the
 // work runs as a launch of its own (k_after_step) or in extra blocks of
 // the force kernel's launch.
-// Lanes per particle of the coupling kernel (outside recording): two with
-// four corners each for the cube, eight with up to four sites each for the
-// three-point stencil.  Fewer lanes repeat less per-particle arithmetic (72
-// against 91 us per MD step with one lane per site of the three-point
-// stencil) until registers limit the waves in flight.
+// Lanes per particle of the coupling kernel (outside recording) where no
+// launch shape sets them: eight with up to four sites each for the three-point
+// stencil (16: 914 against 884 us for three cycles of 128^3 with 12,500
+// particles).  For the cube, fewer lanes repeat less per-particle arithmetic,
+// more lanes have a shorter chain each: as many as leave the 1024 SIMDs about
+// one wavefront each, eight with one corner up to 8192 particles, four up to
+// 16,384, else two with four corners.  Measured with two, four and eight, us a
+// pass: 2000 particles 291/278/269, 10,000 beads 789/752/767 (WCA) and
+// 813/774/786 (Kremer-Grest), 5 x 2560 beads 1579/1543/1607, 40,000 particles
+// 672/673/695, 100,000 2771/2777/-.
+constexpr int kIntervalLanes = 2;  // (k_interval: one CU's issue rate counts)
 template <int ST>
-struct DirectShape {
-  static constexpr int kLanes = ST == 0 ? 2 : 8;
-  static constexpr int kPer = (Stencil<ST>::kSites + kLanes - 1) / kLanes;
-};
+inline int default_lanes(int64_t N) {
+  if (ST == 1) return 8;
+  return N <= 8192 ? 8 : (N <= 16384 ? 4 : 2);
+}
 
 // Pre-reduction of a segment's shared-site transfers in LDS (the launch of
 // k_after_step provides the table; the force kernel's extra blocks pass

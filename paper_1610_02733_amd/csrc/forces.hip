@@ -402,7 +402,7 @@ static hipError_t forces_t(Context* c, int substep = 0) {
     constexpr int ST = AfterST >= 0 ? AfterST : 0;
     ca = couple_args<T>(c, substep);
     // the coupling kernel's lanes per particle (tuned or default)
-    L = c->tune.couple_lanes > 0 ? c->tune.couple_lanes : DirectShape<ST>::kLanes;
+    L = c->tune.couple_lanes > 0 ? c->tune.couple_lanes : default_lanes<ST>(a.N);
     per = (Stencil<ST>::kSites + L - 1) / L;
     nseg = (a.N * L + kBlock - 1) / kBlock;
   }

@@ -120,7 +120,7 @@ struct Layout {
 
 // Launch shapes (autotuner): blocks in flight of the persistent kernels
 // (0 = one block per work item) and lanes per particle of the coupling
-// kernel (0 = the default DirectShape; candidates couple_lane_candidates).
+// kernel (0 = default_lanes; candidates couple_lane_candidates).
 struct Tune {
   int lb_blocks;
   int part_blocks;
