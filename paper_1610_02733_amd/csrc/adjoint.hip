@@ -43,8 +43,34 @@ struct AdjLBArgs {
 // recorded (the sites the MD steps touched).  The derivatives of the result
 // with respect to the relaxation factors are summed per block.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_collide_stream_adjoint(AdjLBArgs<T> a) {
+//
+// Off: the type of the entries' offsets, 32 bits where the lattice allows (half
+// the registers); the pull and the push each compute theirs.  FP32 is held to
+// 4 waves per SIMD, which is one round of the chip at 64^3.  The pushed runs
+// are shifted, so two wavefronts share their end lines: plain stores, which
+// the caches merge (16.1 us at 64^3 streamed, 17.7 plain, but then 12.4 against
+// 9.1 us for the fold that follows; ten cycles of 160 x 144 x 128 with two MD
+// steps 5.80 against 5.42 ms).
+template <typename T, typename Off>
+__device__ __forceinline__ void adjoint_offsets(const Geom& g, int x, int y, int z, Off off[19]) {
+  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
+  const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
+  const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
+  const int X[3] = {xm, x, xp}, Y[3] = {ym * g.nx, y * g.nx, yp * g.nx};
+  const Off A = (Off)g.A, Z[3] = {(Off)zm * 19 * A, (Off)z * 19 * A, (Off)zp * 19 * A};
+  // (the source is r - c: the lower neighbour for c = +1)
+  constexpr int8_t c[19][3] = {{0, 0, 0},   {1, 0, 0},   {-1, 0, 0}, {0, 1, 0},  {0, -1, 0},
+                               {0, 0, 1},   {0, 0, -1},  {1, 1, 0},  {-1, -1, 0}, {1, -1, 0},
+                               {-1, 1, 0},  {1, 0, 1},   {-1, 0, -1}, {1, 0, -1}, {-1, 0, 1},
+                               {0, 1, 1},   {0, -1, -1}, {0, 1, -1}, {0, -1, 1}};
+#pragma unroll
+  for (int i = 0; i < 19; ++i)
+    off[i] = Z[1 - c[i][2]] + (Off)(Y[1 - c[i][1]] + X[1 - c[i][0]]);
+}
+
+template <typename T, typename Off>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 1) void k_collide_stream_adjoint(
+    AdjLBArgs<T> a) {
   const RepLB<T>& q = a.rep[0];
   const uint32_t step_lo = (uint32_t)((unsigned long long)a.t_lb & 0xFFFFFFFFull);
   const uint32_t step_hi = (uint32_t)((unsigned long long)a.t_lb >> 32);
@@ -52,14 +78,14 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream_adjoint(AdjLBArgs<T> 
   for (int r = blockIdx.x * kBlock + threadIdx.x; r < q.g.S; r += gridDim.x * kBlock) {
     int x, y, z;
     site_coords(q.g, r, x, y, z);
-    size_t off[19];
-    pull_offsets(q.g, x, y, z, off);
-    const size_t own = pop_offset(q.g, 0, x, y, z);
+    Off off[19];
+    adjoint_offsets<T>(q.g, x, y, z, off);
+    const Off own = (Off)z * 19 * (Off)q.g.A + (Off)(y * q.g.nx + x);
     T d[19], dbo[19], dbi[19];
 #pragma unroll
     for (int i = 0; i < 19; ++i) {
-      d[i] = __builtin_nontemporal_load(a.src + off[i]);
-      dbo[i] = __builtin_nontemporal_load(a.pin + own + (size_t)i * q.g.A);
+      d[i] = __builtin_nontemporal_load(a.src + (size_t)i * q.g.A + off[i]);
+      dbo[i] = __builtin_nontemporal_load(a.pin + (size_t)i * q.g.A + own);
     }
     const bool marked = (a.mrec[r >> 6] >> (r & 63)) & 1ull;
     T Fx = q.k.g[0], Fy = q.k.g[1], Fz = q.k.g[2];
@@ -78,9 +104,10 @@ __global__ __launch_bounds__(kBlock) void k_collide_stream_adjoint(AdjLBArgs<T> 
     }
     T Fbx, Fby, Fbz, gb[3];
     collide_deviation_adjoint<T>(d, Fx, Fy, Fz, hw, q.k, dbo, dbi, Fbx, Fby, Fbz, gb);
+    asm("" : "+v"(x), "+v"(y), "+v"(z));  // (the offsets are not kept through the collision)
+    adjoint_offsets<T>(q.g, x, y, z, off);
 #pragma unroll
-    for (int i = 0; i < 19; ++i)
-      __builtin_nontemporal_store(dbi[i], a.pout + off[i]);
+    for (int i = 0; i < 19; ++i) a.pout[(size_t)i * q.g.A + off[i]] = dbi[i];
     if (marked) a.jbar[r] = Vec4<T>{Fbx, Fby, Fbz, T(0)};
     acc[0] += (double)gb[0];
     acc[1] += (double)gb[1];
@@ -153,12 +180,13 @@ struct AdjMDArgs {
 //   J_k += -w_k tau Fc                   (transfer, Eq. 7-8)
 //   V1  = V + h (f + Fc);  X' = X + tau V1;  V' = V1 + h (f + Fc)
 // Reverse: from X'-bar, V'-bar and J-bar at the corners, the adjoints of X,
-// V, Fc, u, gamma and f.  Sums over corners are butterfly sums over the
-// lanes; the weights are piecewise linear in X, so their slopes enter
+// V, Fc, u, gamma and f.  Sums over corners are DPP sums over the lanes; the weights are piecewise linear in X, so their slopes enter
 // through both the interpolation and the transfer.  The reads of the
 // interpolation then have adjoints
 //   j-bar_k += w_k / rho_k u-bar,   rho-bar_k -= w_k / rho_k^2 (U_k . u-bar),
-// which Fused adds right here (variant 1: J-bar is not read again in this
+// (5.2 us per MD step of 1000 particles, a chain of loads and some 200 dependent
+// FP64 instructions; 5.9 with the squared weights' sums taken over the lanes
+// and every lane sum through LDS), which Fused adds right here (variant 1: J-bar is not read again in this
 // step); in variant 2 the read includes J, so J-bar gains the same j-bar,
 // and the adds wait for k_scatter_adjoint until every particle of the step
 // has read J-bar.
@@ -167,7 +195,7 @@ template <typename T, bool Fused>
 __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
                                                            const Vec4<T>* __restrict__ jbar,
                                                            Vec4<T>* __restrict__ abar) {
-  const RepMD& m = a.md[0];
+  const RepMD m = scalar_copy(a.md);
   const int64_t N = a.N;
   const unsigned long long t_md = (unsigned long long)a.t_md;
   const uint32_t step_lo = (uint32_t)(t_md & 0xFFFFFFFFull), step_hi = (uint32_t)(t_md >> 32);
@@ -184,14 +212,14 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
     }
     if (!isfinite(X[0])) continue;  // skipped by the forward step (all 8 lanes)
     Cube q;
-    cube_of(X, m.g, q);
+    locate<0>(X, m.g, q);
     int cx, cy, cz, site;
-    double w;
-    corner_of(q, m.g, k, cx, cy, cz, site, w);
-    // d w_k / d s_e
+    stencil_site<0>(q, m.g, k, cx, cy, cz, site);
+    // w_k and d w_k / d s_e
     const double a0 = (k & 1) ? q.s[0] : 1.0 - q.s[0], e0 = (k & 1) ? 1.0 : -1.0;
     const double a1 = (k & 2) ? q.s[1] : 1.0 - q.s[1], e1 = (k & 2) ? 1.0 : -1.0;
     const double a2 = (k & 4) ? q.s[2] : 1.0 - q.s[2], e2 = (k & 4) ? 1.0 : -1.0;
+    const double w = a0 * a1 * a2;
     const double dw[3] = {e0 * a1 * a2, a0 * e1 * a2, a0 * a1 * e2};
     const double ir = r[(30 + k) * N + p];
     const double U[3] = {r[(6 + 3 * k) * N + p], r[(7 + 3 * k) * N + p], r[(8 + 3 * k) * N + p]};
@@ -199,13 +227,18 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
     const double jbv[3] = {(double)jb.x, (double)jb.y, (double)jb.z};
     double u[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) u[d] = oct_sum(w * ir * U[d]);
+    for (int d = 0; d < 3; ++d) u[d] = group_sum<8>(w * ir * U[d]);
     // noise amplitude A(gamma, S) and its derivatives (zero where A = 0:
     // gamma = 0, or the balance factor clamped)
-    const double S = oct_sum(w * w);
-    double dS[3];
+    // (S is the product of the axes' squared sums (1 - s)^2 + s^2)
+    double sq[3], ds[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) dS[d] = oct_sum(2.0 * w * dw[d]);
+    for (int d = 0; d < 3; ++d) {
+      sq[d] = (1.0 - q.s[d]) * (1.0 - q.s[d]) + q.s[d] * q.s[d];
+      ds[d] = 4.0 * q.s[d] - 2.0;
+    }
+    const double S = sq[0] * sq[1] * sq[2];
+    const double dS[3] = {ds[0] * sq[1] * sq[2], sq[0] * ds[1] * sq[2], sq[0] * sq[1] * ds[2]};
     const double A = m.noise ? noise_amplitude(m, S) : 0.0;
     const double c2 = m.gamma > 0.0 ? m.amp * m.amp / m.gamma : 0.0;  // 2 kT / tau
     const double a_damp = 2.0 * (1.0 - noise_balance(m, S));
@@ -236,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
     double xs[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      Fcb[d] += oct_sum(-m.tau * w * jbv[d]);
+      Fcb[d] += group_sum<8>(-m.tau * w * jbv[d]);
       xs[d] = -m.tau * gk * dw[d];
     }
     // friction and noise
@@ -251,7 +284,7 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
     // interpolation weights (through u, the transfer and the noise amplitude)
     const double uk = ir * (U[0] * ub[0] + U[1] * ub[1] + U[2] * ub[2]);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) xs[d] = oct_sum(xs[d] + uk * dw[d]) + nb * dA_dS * dS[d];
+    for (int d = 0; d < 3; ++d) xs[d] = group_sum<8>(xs[d] + uk * dw[d]) + nb * dA_dS * dS[d];
     if (k == 0) {
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
@@ -279,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_scatter_adjoint(AdjMDArgs a, Vec4<T>* __restrict__ abar,
                                                             Vec4<T>* __restrict__ jbar) {
-  const RepMD& m = a.md[0];
+  const RepMD m = scalar_copy(a.md);
   const int64_t N = a.N;
   for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < N * 32;
        t += (int64_t)gridDim.x * kBlock) {
@@ -291,10 +324,11 @@ __global__ __launch_bounds__(kBlock) void k_scatter_adjoint(AdjMDArgs a, Vec4<T>
     for (int d = 0; d < 3; ++d) X[d] = r[d * N + p];
     if (!isfinite(X[0])) continue;
     Cube q;
-    cube_of(X, m.g, q);
+    locate<0>(X, m.g, q);
     int cx, cy, cz, site;
-    double w;
-    corner_of(q, m.g, k, cx, cy, cz, site, w);
+    stencil_site<0>(q, m.g, k, cx, cy, cz, site);
+    const double w = ((k & 1) ? q.s[0] : 1.0 - q.s[0]) * ((k & 2) ? q.s[1] : 1.0 - q.s[1]) *
+                     ((k & 4) ? q.s[2] : 1.0 - q.s[2]);
     const double ir = r[(30 + k) * N + p];
     T* dst = (T*)(abar + site);
     if (c == 3) {
@@ -330,7 +364,12 @@ static hipError_t lb_adjoint_t(Context* c) {
   a.nuacc = (double*)(s.ws + L.nuacc);
   a.t_lb = (long long)s.t_lb[j];
   const int blocks = (int)std::min<int64_t>(kAdjBlocks, (c->plan.Stot + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL(k_collide_stream_adjoint<T>, dim3(blocks), dim3(kBlock), 0, c->stream, a);
+  if (19ull * (unsigned long long)c->plan.Stot < (1ull << 32))
+    hipLaunchKernelGGL((k_collide_stream_adjoint<T, uint32_t>), dim3(blocks), dim3(kBlock), 0,
+                       c->stream, a);
+  else
+    hipLaunchKernelGGL((k_collide_stream_adjoint<T, size_t>), dim3(blocks), dim3(kBlock), 0,
+                       c->stream, a);
   return hipGetLastError();
 }
 

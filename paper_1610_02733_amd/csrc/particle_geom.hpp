@@ -134,13 +134,6 @@ __device__ __forceinline__ double noise_amplitude(const RepMD& m, double S) {
 // so the lanes of a particle are always active together).
 constexpr int kCornerLanes = 8;
 
-__device__ __forceinline__ double oct_sum(double v) {  // over the 8 lanes of a particle
-  v += __shfl_xor(v, 1, kCornerLanes);
-  v += __shfl_xor(v, 2, kCornerLanes);
-  v += __shfl_xor(v, 4, kCornerLanes);
-  return v;
-}
-
 // ---------------------------------------------------------------------------
 // Interpolation / spreading stencils (Eq. 5 and Eq. 7 use the same one).
 // A particle's stencil is described by a Cube: the lowest site index per
