@@ -441,17 +441,41 @@ hipError_t launch_adjoint_fold(Context* c) {
   return c->plan.prec == 32 ? fold_t<float>(c) : fold_t<double>(c);
 }
 
-// Counters of a saved state, written on the stream like the rest of it.
-__global__ void k_store_counters(long long* __restrict__ dst, long long t_lb, long long t_md) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    dst[0] = t_lb;
-    dst[1] = t_md;
+// Sums of the swept cycles' derivatives: out[0..3] over the particles (pacc),
+// out[4], out[5] over the blocks of the reverse LB step (nuacc, bulk and
+// shear).  One block, a fixed order.
+__global__ __launch_bounds__(kBlock) void k_adjoint_totals(const double* __restrict__ pacc,
+                                                           int64_t N,
+                                                           const double* __restrict__ nuacc,
+                                                           double* __restrict__ out) {
+  __shared__ double sh[kBlock / 64][6];
+  double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int64_t p = threadIdx.x; p < N; p += kBlock)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k] += pacc[k * N + p];
+  for (int b = threadIdx.x; b < kAdjBlocks; b += kBlock)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) acc[4 + k] += nuacc[(size_t)b * 4 + k];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    double s = acc[k];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    if (lane == 0) sh[wv][k] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    double s = 0.0;
+    for (int w = 0; w < kBlock / 64; ++w) s += sh[w][threadIdx.x];
+    out[threadIdx.x] = s;
   }
 }
 
-hipError_t launch_store_counters(Context* c, void* dst, int64_t t_lb, int64_t t_md) {
-  hipLaunchKernelGGL(k_store_counters, dim3(1), dim3(64), 0, c->stream, (long long*)dst,
-                     (long long)t_lb, (long long)t_md);
+hipError_t launch_adjoint_totals(Context* c, double* d_out) {
+  const AdjState& s = c->adj;
+  hipLaunchKernelGGL(k_adjoint_totals, dim3(1), dim3(kBlock), 0, c->stream,
+                     (const double*)(s.ws + s.lay.pacc), c->plan.Ntot,
+                     (const double*)(s.ws + s.lay.nuacc), d_out);
   return hipGetLastError();
 }
 

@@ -249,53 +249,43 @@ int fail(Context* c, hipError_t e) {
   return LBMD_EHIP;
 }
 
-// Per-replica tables and the clock, uploaded once at creation.
+// Per-replica tables and the clock, uploaded once at creation (the workspace is
+// zero, which is a single system's part_rep and the clock).
 hipError_t upload_tables(Context* c) {
   const Plan& pl = c->plan;
   const int R = pl.R;
-  hipError_t e;
-  if (pl.prec == 32) {
-    std::vector<RepLB<float>> lb(R);
-    for (int r = 0; r < R; ++r) lb[r] = rep_lb<float>(c, r);
-    e = hipMemcpyAsync(at(c, pl.lay.rep_lb), lb.data(), sizeof(RepLB<float>) * R,
-                       hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  } else {
-    std::vector<RepLB<double>> lb(R);
-    for (int r = 0; r < R; ++r) lb[r] = rep_lb<double>(c, r);
-    e = hipMemcpyAsync(at(c, pl.lay.rep_lb), lb.data(), sizeof(RepLB<double>) * R,
-                       hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  }
-  if (e != hipSuccess) return e;
+  std::vector<RepLB<float>> lb32(pl.prec == 32 ? R : 0);
+  std::vector<RepLB<double>> lb64(pl.prec == 32 ? 0 : R);
   std::vector<RepMD> md(R);
-  for (int r = 0; r < R; ++r) md[r] = rep_md(c, r);
+  for (int r = 0; r < R; ++r) {
+    if (pl.prec == 32)
+      lb32[r] = rep_lb<float>(c, r);
+    else
+      lb64[r] = rep_lb<double>(c, r);
+    md[r] = rep_md(c, r);
+  }
+  if (R == 1) return launch_tables_one(c, lb32.data(), lb64.data(), md[0]);
   std::vector<int32_t> items(pl.item_off.begin(), pl.item_off.end());
   std::vector<int32_t> prep((size_t)std::max<int64_t>(pl.Ntot, 1), 0);
   for (int r = 0; r < R; ++r)
     for (int q = 0; q < c->p[r].n_particles; ++q) prep[pl.part_off[r] + q] = r;
-  Clock clk{0, 0, 0, 0};
-  if ((e = hipMemcpyAsync(at(c, pl.lay.rep_md), md.data(), sizeof(RepMD) * R,
-                          hipMemcpyHostToDevice, c->stream)) != hipSuccess)
-    return e;
-  if ((e = hipMemcpyAsync(at(c, pl.lay.item_rep), items.data(), sizeof(int32_t) * items.size(),
-                          hipMemcpyHostToDevice, c->stream)) != hipSuccess)
-    return e;
-  if ((e = hipMemcpyAsync(at(c, pl.lay.part_rep), prep.data(), sizeof(int32_t) * prep.size(),
-                          hipMemcpyHostToDevice, c->stream)) != hipSuccess)
-    return e;
-  if ((e = hipMemcpyAsync(at(c, pl.lay.clock), &clk, sizeof(clk), hipMemcpyHostToDevice,
-                          c->stream)) != hipSuccess)
-    return e;
-  return hipStreamSynchronize(c->stream);
+  const auto up_to = [&](size_t off, const void* src, size_t bytes) {
+    return hipMemcpyAsync(at(c, off), src, bytes, hipMemcpyHostToDevice, c->stream);
+  };
+  hipError_t e = pl.prec == 32 ? up_to(pl.lay.rep_lb, lb32.data(), sizeof(RepLB<float>) * R)
+                               : up_to(pl.lay.rep_lb, lb64.data(), sizeof(RepLB<double>) * R);
+  if (e == hipSuccess) e = up_to(pl.lay.rep_md, md.data(), sizeof(RepMD) * R);
+  if (e == hipSuccess) e = up_to(pl.lay.item_rep, items.data(), sizeof(int32_t) * items.size());
+  if (e == hipSuccess) e = up_to(pl.lay.part_rep, prep.data(), sizeof(int32_t) * prep.size());
+  // (the sources are released on return)
+  const hipError_t e2 = hipStreamSynchronize(c->stream);
+  return e == hipSuccess ? e2 : e;
 }
 
-hipError_t write_clock(Context* c) {
-  Clock clk{(long long)c->t_lb, (long long)(c->t_md - c->subs), c->cur, 0};
-  hipError_t e = hipMemcpyAsync(clock_of(c, c->clk), &clk, sizeof(clk), hipMemcpyHostToDevice,
-                                c->stream);
-  if (e != hipSuccess) return e;
-  return hipStreamSynchronize(c->stream);
+// The current clock entry from the host's counters.
+void set_clock(Context* c, RegionOps& ops) {
+  ops.clock = clock_of(c, c->clk);
+  ops.clock_value = Clock{(long long)c->t_lb, (long long)(c->t_md - c->subs), c->cur, 0};
 }
 
 void drop_graph(lbmd* c) {
@@ -313,12 +303,24 @@ void drop_graph(lbmd* c) {
 // binding, and where the step counters or the particles are set from
 // outside.  The next MD step refills the cache, which records every
 // particle's stencil again.
+void reset_stencil_records(Context* c, RegionOps& ops) {
+  ops.fill(at(c, c->plan.lay.owner), 0xFFFFFFFFu, (size_t)c->plan.Stot * 4);
+  ops.fill(at(c, c->plan.lay.moved_at), 0xFFFFFFFFu, (size_t)c->plan.Ntot * 8);
+}
 hipError_t reset_stencil_records(Context* c) {
-  hipError_t e = hipMemsetAsync(at(c, c->plan.lay.owner), 0xFF, (size_t)c->plan.Stot * 4,
-                                c->stream);
-  if (e == hipSuccess && c->plan.Ntot > 0)
-    e = hipMemsetAsync(at(c, c->plan.lay.moved_at), 0xFF, (size_t)c->plan.Ntot * 8, c->stream);
-  return e;
+  RegionOps ops;
+  reset_stencil_records(c, ops);
+  return launch_region_ops(ops, c->stream);
+}
+
+// Whether the caller is capturing the context's stream in a graph.
+bool being_captured(hipStream_t stream) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return s == hipStreamCaptureStatusActive;
 }
 
 int create(const lbmd_params* p, int32_t R, void* d_ws, size_t ws_bytes, void* hip_stream,
@@ -355,7 +357,8 @@ int create(const lbmd_params* p, int32_t R, void* d_ws, size_t ws_bytes, void* h
   c->rec_mark = nullptr;
   c->scratch_rows = nullptr;
   // fluid at rest (all deviations zero), nothing transferred yet
-  hipError_t e = hipMemsetAsync(c->ws, 0, pl.lay.total, c->stream);
+  hipError_t e = being_captured(c->stream) ? hipErrorStreamCaptureUnsupported : hipSuccess;
+  if (e == hipSuccess) e = hipMemsetAsync(c->ws, 0, pl.lay.total, c->stream);
   if (e == hipSuccess) e = reset_stencil_records(c);
   if (e == hipSuccess) e = upload_tables(c);
   // set-up of lb_moments_noalloc: this GPU's address of the library's fixed
@@ -379,16 +382,6 @@ hipError_t substep_launches(Context* c, int substep) {
   hipError_t e = launch_couple(c, substep);
   if (e == hipSuccess && c->plan.any_forces2) e = launch_forces_and_kick(c, substep);
   return e;
-}
-
-// Whether the caller is capturing the context's stream in a graph.
-bool being_captured(hipStream_t stream) {
-  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &s) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return s == hipStreamCaptureStatusActive;
 }
 
 // One LB step after md_steps MD steps; the device clock (in place for a
@@ -601,18 +594,14 @@ static int moments_common(lbmd* c, int32_t rep, void* d_rho, void* d_u, double* 
   if (!rc) rc = fail(c, launch_moments(c, rep, d_rho, d_u, d_tot));
   if (rc || !h_totals) return rc;
   std::vector<double> tot((size_t)R * kRedWidth);
-  int32_t flags[16];
   rc = fail(c, hipMemcpyAsync(tot.data(), d_tot, sizeof(double) * tot.size(),
                               hipMemcpyDeviceToHost, c->stream));
-  if (!rc)
-    rc = fail(c, hipMemcpyAsync(flags, at(c, c->plan.lay.flags), sizeof(flags),
-                                hipMemcpyDeviceToHost, c->stream));
   if (!rc) rc = fail(c, hipStreamSynchronize(c->stream));
   if (rc) return rc;
   const int r0 = all ? 0 : rep, r1 = all ? R : rep + 1;
   for (int r = r0; r < r1; ++r)
     fill_totals(c, r, &tot[(size_t)r * kRedWidth], h_totals + (size_t)(all ? r : 0) * LBMD_NTOTALS);
-  return flags[0] ? LBMD_ENONFINITE : LBMD_OK;
+  return tot[12] != 0.0 ? LBMD_ENONFINITE : LBMD_OK;
 }
 
 int lb_moments(lbmd* c, void* d_rho, void* d_u, double* h_totals) {
@@ -632,16 +621,12 @@ int lb_moments_noalloc(lbmd* c, void* d_rho, void* d_u, double* h_totals) {
   if (!rc) rc = fail(c, launch_moments_rows(c, d_rho, d_u, c->scratch_rows));
   if (rc || !h_totals) return rc;
   double tot[kRedWidth];
-  int32_t flags[16];
   rc = fail(c, hipMemcpyAsync(tot, c->scratch_rows + (size_t)kScratchRows * kRedWidth,
                               sizeof(tot), hipMemcpyDeviceToHost, c->stream));
-  if (!rc)
-    rc = fail(c, hipMemcpyAsync(flags, at(c, c->plan.lay.flags), sizeof(flags),
-                                hipMemcpyDeviceToHost, c->stream));
   if (!rc) rc = fail(c, hipStreamSynchronize(c->stream));
   if (rc) return rc;
   fill_totals(c, 0, tot, h_totals);
-  return flags[0] ? LBMD_ENONFINITE : LBMD_OK;
+  return tot[12] != 0.0 ? LBMD_ENONFINITE : LBMD_OK;
 }
 
 int lbmd_batch_moments(lbmd* c, double* h_totals) {
@@ -704,11 +689,15 @@ int lbmd_set_counters(lbmd* c, int64_t t_lb, int64_t t_md, int32_t subs) {
   if (c->sticky) return c->sticky;
   int rc0 = fail(c, launch_leave_transfers(c));  // J complete before the cache is rebuilt
   if (rc0) return rc0;
+  // (the host's counters would be set now, the device's in every replay)
+  if (being_captured(c->stream)) return fail(c, hipErrorStreamCaptureUnsupported);
   c->t_lb = t_lb;
   c->t_md = t_md;
   c->subs = subs;
-  int rc = fail(c, write_clock(c));
-  if (!rc) rc = fail(c, reset_stencil_records(c));
+  RegionOps ops;
+  set_clock(c, ops);
+  reset_stencil_records(c, ops);
+  int rc = fail(c, launch_region_ops(ops, c->stream));
   // the force cells are kept in halves by MD-step parity: bin again under
   // the new count
   if (!rc && c->bound && c->plan.any_forces2) rc = fail(c, launch_forces(c));
@@ -774,38 +763,37 @@ bool adjoint_supported(const Context* c) {
          c->p[0].stencil == 0;
 }
 
-// Particles, counters and an empty transfer field from a saved state (the
-// populations are handled by the caller).
-int load_common(lbmd* c, const char* src, const StateLayout& sl) {
+// Particles, counters and an empty transfer field from a saved state, and its
+// populations into `pop` (null: handled by the caller).
+int load_common(lbmd* c, const char* src, const StateLayout& sl, void* pop) {
   const size_t N = (size_t)c->plan.Ntot, S = (size_t)c->plan.Stot;
+  const size_t t = c->plan.prec == 32 ? 4 : 8;
+  RegionOps ops;
+  if (pop) ops.copy(pop, src + sl.pop, 19 * (size_t)c->plan.P * t);
+  if (N > 0) {
+    ops.copy(c->x, src + sl.x, 3 * N * 8);
+    ops.copy(c->v, src + sl.v, 3 * N * 8);
+    ops.copy(c->img, src + sl.img, 3 * N * 4);
+    ops.copy(at(c, c->plan.lay.pid), src + sl.pid, N * 4);
+  }
+  ops.fill(at(c, c->plan.lay.transfer), 0, S * 4 * t);
+  ops.fill(at(c, c->plan.lay.mark), 0, (S / 64) * 8);
+  reset_stencil_records(c, ops);
+  set_clock(c, ops);
+  ops.clock_from = src + sl.counters;
+  int rc = fail(c, launch_region_ops(ops, c->stream));
   long long cnt[2];
-  int rc = fail(c, hipMemcpyAsync(cnt, src + sl.counters, sizeof(cnt), hipMemcpyDeviceToHost,
-                                  c->stream));
+  if (!rc)
+    rc = fail(c, hipMemcpyAsync(cnt, src + sl.counters, sizeof(cnt), hipMemcpyDeviceToHost,
+                                c->stream));
+  // (the state is the caller's again on return)
   if (!rc) rc = fail(c, hipStreamSynchronize(c->stream));
   if (rc) return rc;
   if (cnt[0] < 0 || cnt[1] < 0) return LBMD_EINVAL;
-  if (N > 0) {
-    rc = fail(c, hipMemcpyAsync(c->x, src + sl.x, 3 * N * 8, hipMemcpyDeviceToDevice, c->stream));
-    if (!rc)
-      rc = fail(c, hipMemcpyAsync(c->v, src + sl.v, 3 * N * 8, hipMemcpyDeviceToDevice, c->stream));
-    if (!rc)
-      rc = fail(c, hipMemcpyAsync(c->img, src + sl.img, 3 * N * 4, hipMemcpyDeviceToDevice,
-                                  c->stream));
-    if (!rc)
-      rc = fail(c, hipMemcpyAsync(at(c, c->plan.lay.pid), src + sl.pid, N * 4,
-                                  hipMemcpyDeviceToDevice, c->stream));
-    if (rc) return rc;
-  }
-  const size_t t = c->plan.prec == 32 ? 4 : 8;
-  rc = fail(c, hipMemsetAsync(at(c, c->plan.lay.transfer), 0, S * 4 * t, c->stream));
-  if (!rc) rc = fail(c, hipMemsetAsync(at(c, c->plan.lay.mark), 0, (S / 64) * 8, c->stream));
-  if (rc) return rc;
   c->t_lb = cnt[0];
   c->t_md = cnt[1];
   c->subs = 0;
-  rc = fail(c, write_clock(c));
-  if (!rc) rc = fail(c, reset_stencil_records(c));
-  if (!rc) rc = fail(c, invalidate_corner_cache(c));
+  rc = fail(c, invalidate_corner_cache(c));
   if (!rc && c->bound) rc = fail(c, launch_init_forces(c));
   return rc;
 }
@@ -825,22 +813,18 @@ int lbmd_save_state(lbmd* c, void* d_dst) {
   char* dst = (char*)d_dst;
   const size_t N = (size_t)c->plan.Ntot;
   const size_t t = c->plan.prec == 32 ? 4 : 8;
-  int rc = fail(c, launch_store_counters(c, dst + sl.counters, c->t_lb, c->t_md));
-  if (!rc)
-    rc = fail(c, hipMemcpyAsync(dst + sl.pop, c->popv[c->cur], 19 * (size_t)c->plan.P * t,
-                                hipMemcpyDeviceToDevice, c->stream));
-  if (!rc && N > 0) {
-    rc = fail(c, hipMemcpyAsync(dst + sl.x, c->x, 3 * N * 8, hipMemcpyDeviceToDevice, c->stream));
-    if (!rc)
-      rc = fail(c, hipMemcpyAsync(dst + sl.v, c->v, 3 * N * 8, hipMemcpyDeviceToDevice, c->stream));
-    if (!rc)
-      rc = fail(c, hipMemcpyAsync(dst + sl.img, c->img, 3 * N * 4, hipMemcpyDeviceToDevice,
-                                  c->stream));
-    if (!rc)
-      rc = fail(c, hipMemcpyAsync(dst + sl.pid, at(c, c->plan.lay.pid), N * 4,
-                                  hipMemcpyDeviceToDevice, c->stream));
+  RegionOps ops;
+  ops.counters = dst + sl.counters;
+  ops.counter_value[0] = c->t_lb;
+  ops.counter_value[1] = c->t_md;
+  ops.copy(dst + sl.pop, c->popv[c->cur], 19 * (size_t)c->plan.P * t);
+  if (N > 0) {
+    ops.copy(dst + sl.x, c->x, 3 * N * 8);
+    ops.copy(dst + sl.v, c->v, 3 * N * 8);
+    ops.copy(dst + sl.img, c->img, 3 * N * 4);
+    ops.copy(dst + sl.pid, at(c, c->plan.lay.pid), N * 4);
   }
-  return rc;
+  return fail(c, launch_region_ops(ops, c->stream));
 }
 
 int lbmd_load_state(lbmd* c, const void* d_src) {
@@ -848,12 +832,7 @@ int lbmd_load_state(lbmd* c, const void* d_src) {
   if (c->sticky) return c->sticky;
   if (c->plan.Ntot > 0 && !c->bound) return LBMD_ESTATE;
   const StateLayout sl = state_layout(c);
-  const char* src = (const char*)d_src;
-  const size_t t = c->plan.prec == 32 ? 4 : 8;
-  int rc = fail(c, hipMemcpyAsync(c->popv[c->cur], src + sl.pop, 19 * (size_t)c->plan.P * t,
-                                  hipMemcpyDeviceToDevice, c->stream));
-  if (rc) return rc;
-  return load_common(c, src, sl);
+  return load_common(c, (const char*)d_src, sl, c->popv[c->cur]);
 }
 
 size_t lbmd_adjoint_workspace_bytes(lbmd* c, int32_t seg_cycles) {
@@ -910,7 +889,7 @@ int lbmd_adjoint_record(lbmd* c, const void* d_state, int32_t ncycles) {
   if (c->plan.Ntot > 0 && !c->bound) return LBMD_ESTATE;
   const StateLayout sl = state_layout(c);
   const char* st = (const char*)d_state;
-  int rc = load_common(c, st, sl);
+  int rc = load_common(c, st, sl, nullptr);
   if (rc) return rc;
   const AdjLayout& L = a.lay;
   const size_t S = (size_t)c->plan.Stot, N = (size_t)c->plan.Ntot;
@@ -1004,23 +983,14 @@ int lbmd_adjoint_result(lbmd* c, double* d_xbar, double* d_vbar, double* h_grads
     rc = fail(c, hipMemcpyAsync(d_vbar, a.ws + L.vbar, 3 * N * 8, hipMemcpyDeviceToDevice,
                                 c->stream));
   if (rc || !h_grads) return rc;
-  std::vector<double> pacc(4 * N), nuacc((size_t)kAdjBlocks * 4);
-  if (N)
-    rc = fail(c, hipMemcpyAsync(pacc.data(), a.ws + L.pacc, 4 * N * 8, hipMemcpyDeviceToHost,
-                                c->stream));
+  // (the totals row of the context is scratch between calls)
+  double g[6], *d_tot = (double*)at(c, c->plan.lay.totals);
+  rc = fail(c, launch_adjoint_totals(c, d_tot));
   if (!rc)
-    rc = fail(c, hipMemcpyAsync(nuacc.data(), a.ws + L.nuacc, nuacc.size() * 8,
-                                hipMemcpyDeviceToHost, c->stream));
+    rc = fail(c, hipMemcpyAsync(g, d_tot, sizeof(g), hipMemcpyDeviceToHost, c->stream));
   if (!rc) rc = fail(c, hipStreamSynchronize(c->stream));
   if (rc) return rc;
-  double g[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = 0; k < 4; ++k)
-    for (size_t p = 0; p < N; ++p) g[k] += pacc[k * N + p];
-  double gb = 0.0, gs = 0.0;
-  for (int b = 0; b < kAdjBlocks; ++b) {
-    gb += nuacc[(size_t)b * 4 + 0];
-    gs += nuacc[(size_t)b * 4 + 1];
-  }
+  const double gb = g[4], gs = g[5];
   const lbmd_params& p = c->p[0];
   const double dgs_dnu = 12.0 / ((6.0 * p.nu + 1.0) * (6.0 * p.nu + 1.0));
   h_grads[0] = g[0];

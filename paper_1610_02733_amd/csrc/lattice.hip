@@ -524,13 +524,15 @@ __global__ __launch_bounds__(kBlock) void k_moments(StreamArgs<T> a, int per, in
 
 // One block per replica: sum its partial rows (for a single replica one per
 // chunk; else those of its chunks), then its particles' momentum and kinetic
-// energy (columns 8-10 sum v, 11 sum |v|^2).
+// energy (columns 8-10 sum v, 11 sum |v|^2); column 12 is the context's
+// non-finite flag.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_finalize(StreamArgs<T> a,
                                                      const RepMD* __restrict__ md,
                                                      const double* __restrict__ partials,
                                                      const double* __restrict__ v, int64_t Ntot,
-                                                     double* __restrict__ totals, int per) {
+                                                     double* __restrict__ totals, int per,
+                                                     const int32_t* __restrict__ flags) {
   const int rr = blockIdx.x;
   const int i0 = a.item_off[rr], i1 = a.item_off[rr + 1];
   double acc[12];
@@ -552,6 +554,8 @@ __global__ __launch_bounds__(kBlock) void k_finalize(StreamArgs<T> a,
     }
   }
   block_reduce_store<12>(acc, totals + (size_t)rr * kRedWidth);
+  // the non-finite flag travels with the totals (column 12)
+  if (threadIdx.x == 0) totals[(size_t)rr * kRedWidth + 12] = (double)flags[0];
 }
 
 // Items per chunk: one reduction per 4 items once there are enough chunks to
@@ -586,7 +590,8 @@ static hipError_t moments_t(Context* c, int rep, void* d_rho, void* d_u, double*
   if (e != hipSuccess || !d_totals) return e;
   hipLaunchKernelGGL(k_finalize<T>, dim3(c->plan.R), dim3(kBlock), 0, c->stream, a,
                      (const RepMD*)at(c, c->plan.lay.rep_md), partials,
-                     (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot, d_totals, per);
+                     (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot, d_totals, per,
+                     (const int32_t*)at(c, c->plan.lay.flags));
   return hipGetLastError();
 }
 
@@ -638,7 +643,8 @@ static hipError_t moments_rows_t(Context* c, void* d_rho, void* d_u, double* row
   hipLaunchKernelGGL(k_finalize<T>, dim3(1), dim3(kBlock), 0, c->stream, a,
                      (const RepMD*)at(c, c->plan.lay.rep_md), rows,
                      (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot,
-                     rows + (size_t)kScratchRows * kRedWidth, per);
+                     rows + (size_t)kScratchRows * kRedWidth, per,
+                     (const int32_t*)at(c, c->plan.lay.flags));
   return hipGetLastError();
 }
 
@@ -775,6 +781,102 @@ hipError_t launch_set_populations(Context* c, int rep, const void* src) {
 }
 hipError_t launch_get_transfer(Context* c, int rep, void* dst) {
   return c->plan.prec == 32 ? copy_t<float>(c, rep, dst, 2) : copy_t<double>(c, rep, dst, 2);
+}
+
+// ---------------------------------------------------------------------------
+// Regions copied and filled one after the other by the whole grid, 16 bytes a
+// thread where both ends are aligned (RegionOps).  Bound by memory in the
+// large (a state of 256^3 in FP32: saved in 416 us, loaded in 510, against 508
+// and 611 with the runtime's copies), by the launch in the small (32^3: 15 and
+// 26 us, against 18 and 56).  Past the caches' reach (Big) the copies are
+// streamed: kept, 256^3 takes 672 and 807 us.
+// ---------------------------------------------------------------------------
+typedef uint32_t quad __attribute__((ext_vector_type(4)));
+
+template <bool Big>
+__global__ __launch_bounds__(kBlock) void k_region_ops(RegionOps ops) {
+  const size_t t0 = (size_t)blockIdx.x * kBlock + threadIdx.x, stride = (size_t)gridDim.x * kBlock;
+  long long t_lb = ops.clock_value.t_lb, t_md = ops.clock_value.t_md;
+  if (ops.clock_from) {
+    long long cnt[2];
+    __builtin_memcpy(cnt, ops.clock_from, sizeof(cnt));
+    t_lb = cnt[0];
+    t_md = cnt[1];
+    if (t_lb < 0 || t_md < 0) return;
+  }
+  for (int k = 0; k < ops.n; ++k) {
+    uint32_t* __restrict__ dst = ops.op[k].dst;
+    const uint32_t* __restrict__ src = ops.op[k].src;
+    const uint32_t f = ops.op[k].fill;
+    const size_t words = ops.op[k].words;
+    size_t quads = 0;
+    if ((((uintptr_t)dst | (uintptr_t)src) & 15) == 0) {
+      quads = words / 4;
+      quad* __restrict__ d = reinterpret_cast<quad*>(dst);
+      const quad* __restrict__ q = reinterpret_cast<const quad*>(src);
+      if (!src)
+        for (size_t i = t0; i < quads; i += stride) d[i] = quad{f, f, f, f};
+      else if (Big)
+        for (size_t i = t0; i < quads; i += stride)
+          __builtin_nontemporal_store(__builtin_nontemporal_load(q + i), d + i);
+      else
+        for (size_t i = t0; i < quads; i += stride) d[i] = q[i];
+    }
+    for (size_t i = 4 * quads + t0; i < words; i += stride) dst[i] = src ? src[i] : f;
+  }
+  if (t0 == 0 && ops.clock) *ops.clock = Clock{t_lb, t_md, ops.clock_value.cur, 0};
+  if (t0 == 0 && ops.counters)
+    __builtin_memcpy(ops.counters, ops.counter_value, sizeof(ops.counter_value));
+}
+
+hipError_t launch_region_ops(const RegionOps& asked, hipStream_t stream) {
+  RegionOps ops = asked;
+  ops.n = 0;
+  size_t most = 1;
+  for (int k = 0; k < asked.n; ++k) {
+    const RegionOps::Op& o = asked.op[k];
+    if ((((uintptr_t)o.dst | (uintptr_t)o.src) & 3) != 0) {  // (a state at an odd address)
+      const hipError_t e =
+          hipMemcpyAsync(o.dst, o.src, 4 * o.words, hipMemcpyDeviceToDevice, stream);
+      if (e != hipSuccess) return e;
+      continue;
+    }
+    ops.op[ops.n++] = o;
+    most = std::max(most, o.words);
+  }
+  const size_t want = (most / 4 + kBlock - 1) / kBlock;
+  const unsigned grid = (unsigned)std::max<size_t>(1, std::min<size_t>(want, 1u << 22));
+  if (8 * most > ((size_t)256 << 20))  // source and destination past the memory-side cache
+    hipLaunchKernelGGL(k_region_ops<true>, dim3(grid), dim3(kBlock), 0, stream, ops);
+  else
+    hipLaunchKernelGGL(k_region_ops<false>, dim3(grid), dim3(kBlock), 0, stream, ops);
+  return hipGetLastError();
+}
+
+// The tables of a single system, carried as launch arguments.
+template <typename T>
+__global__ void k_tables_one(RepLB<T>* __restrict__ lb, RepLB<T> lb_value, RepMD* __restrict__ md,
+                             RepMD md_value, int32_t* __restrict__ item_off, int nitems) {
+  if (threadIdx.x == 0) {
+    *lb = lb_value;
+    *md = md_value;
+    item_off[0] = 0;
+    item_off[1] = nitems;
+  }
+}
+
+hipError_t launch_tables_one(Context* c, const RepLB<float>* lb32, const RepLB<double>* lb64,
+                             const RepMD& md) {
+  const Layout& L = c->plan.lay;
+  if (lb32)
+    hipLaunchKernelGGL(k_tables_one<float>, dim3(1), dim3(64), 0, c->stream,
+                       (RepLB<float>*)at(c, L.rep_lb), *lb32, (RepMD*)at(c, L.rep_md), md,
+                       (int32_t*)at(c, L.item_rep), c->plan.nitems);
+  else
+    hipLaunchKernelGGL(k_tables_one<double>, dim3(1), dim3(64), 0, c->stream,
+                       (RepLB<double>*)at(c, L.rep_lb), *lb64, (RepMD*)at(c, L.rep_md), md,
+                       (int32_t*)at(c, L.item_rep), c->plan.nitems);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

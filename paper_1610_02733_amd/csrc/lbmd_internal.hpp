@@ -233,12 +233,42 @@ __device__ __forceinline__ U scalar_copy(const U* p) {
   return out;
 }
 
+// Copies and fills of whole regions in one launch (launch_region_ops): saved
+// states, resets.  A call of its own for each costs a launch and, for a host
+// source, a synchronisation; the clock and a state's counters travel as
+// arguments.  A state read back sets the clock's counters on the device, and
+// where they are negative nothing is written.
+struct RegionOps {
+  static constexpr int kMax = 10;
+  struct Op {
+    uint32_t* dst;
+    const uint32_t* src;  // null: fill
+    uint32_t fill;
+    size_t words;  // 32-bit words
+  } op[kMax];
+  int n = 0;
+  Clock* clock = nullptr;  // written when set
+  Clock clock_value;
+  const char* clock_from = nullptr;  // counters of the clock read here when set (any address)
+  char* counters = nullptr;          // two values written here when set (any address)
+  long long counter_value[2];
+  void copy(void* dst, const void* src, size_t bytes) {
+    if (bytes) op[n++] = {(uint32_t*)dst, (const uint32_t*)src, 0u, bytes / 4};
+  }
+  void fill(void* dst, uint32_t value, size_t bytes) {
+    if (bytes) op[n++] = {(uint32_t*)dst, nullptr, value, bytes / 4};
+  }
+};
+
 // Launchers (return hipError_t of the launch).
+hipError_t launch_region_ops(const RegionOps& ops, hipStream_t stream);
+hipError_t launch_tables_one(Context* c, const RepLB<float>* lb32, const RepLB<double>* lb64,
+                             const RepMD& md);
+hipError_t launch_adjoint_totals(Context* c, double* d_out);
 hipError_t launch_collide_stream(Context* c, Clock* next, int md_steps);
 hipError_t launch_collide_stream_adjoint(Context* c);
 hipError_t launch_couple_adjoint(Context* c);
 hipError_t launch_adjoint_fold(Context* c);
-hipError_t launch_store_counters(Context* c, void* dst, int64_t t_lb, int64_t t_md);
 hipError_t launch_clock_advance(Context* c, int md_steps);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 size_t sort_temp_bytes(int64_t N);
