@@ -24,9 +24,10 @@ struct AdjLBArgs {
   const T* __restrict__ src;                  // populations the cycle read (slot)
   const T* __restrict__ pin;                  // adjoint of the cycle's output
   T* __restrict__ pout;                       // adjoint of the cycle's input
-  const Vec4<T>* __restrict__ jrec;           // J at the LB step (marked sites)
+  const Vec4<T>* jrec;                        // J at the LB step (marked sites)
   const unsigned long long* __restrict__ mrec;
-  Vec4<T>* __restrict__ jbar;
+  Vec4<T>* jbar;
+  Vec4<T>* clear;                             // set to zero where J was recorded, or null (may be jrec)
   const RepLB<T>* __restrict__ rep;
   double* __restrict__ nuacc;                 // [gridDim][4]
   long long t_lb;
@@ -108,7 +109,10 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 1) void k_collide_stre
     adjoint_offsets<T>(q.g, x, y, z, off);
 #pragma unroll
     for (int i = 0; i < 19; ++i) a.pout[(size_t)i * q.g.A + off[i]] = dbi[i];
-    if (marked) a.jbar[r] = Vec4<T>{Fbx, Fby, Fbz, T(0)};
+    if (marked) {
+      a.jbar[r] = Vec4<T>{Fbx, Fby, Fbz, T(0)};
+      if (a.clear) a.clear[r] = Vec4<T>{T(0), T(0), T(0), T(0)};
+    }
     acc[0] += (double)gb[0];
     acc[1] += (double)gb[1];
     acc[2] += (double)gb[2];
@@ -157,17 +161,54 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_fold(const RepLB<T>* __restr
 }
 
 struct AdjMDArgs {
-  const double* __restrict__ rec;  // [kAdjRec][N] record of this MD step
+  double* rec;                     // [kAdjRec][N] record of this MD step
+  const double* prev;              // that of the step reversed before it in this cycle, or null
+  bool more;                       // another MD step of this cycle follows
   const double* __restrict__ fcons;
   double* __restrict__ xbar;
   double* __restrict__ vbar;
-  double* __restrict__ ubar;
   double* __restrict__ pacc;       // [4][N]
   const RepMD* __restrict__ md;
   const int32_t* __restrict__ pid;  // particle identity of each slot (noise counter)
   int64_t N;
   long long t_md;                  // MD step being reversed
 };
+
+// Adds of four components a lane, `site` per lane (negative: none).  The four
+// lanes of a quad take each other's sites in turn, a component each, so that
+// one instruction adds 16 whole sites (one request each) instead of one
+// component of 64.
+template <int Ctrl>
+__device__ __forceinline__ int quad_of(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, Ctrl, 0xF, 0xF, false);
+}
+template <int Ctrl>
+__device__ __forceinline__ float quad_of(float v) {
+  return __int_as_float(quad_of<Ctrl>(__float_as_int(v)));
+}
+template <int Ctrl>
+__device__ __forceinline__ double quad_of(double v) {
+  return __hiloint2double(quad_of<Ctrl>(__double2hiint(v)), quad_of<Ctrl>(__double2loint(v)));
+}
+template <typename T, int From>
+__device__ __forceinline__ void quad_add(Vec4<T>* field, int site, const T add[4], int comps) {
+  constexpr int ctrl = From * 0x55;  // quad_perm: every lane takes lane From
+  const int c = threadIdx.x & 3;
+  const T v0 = quad_of<ctrl>(add[0]), v1 = quad_of<ctrl>(add[1]), v2 = quad_of<ctrl>(add[2]),
+          v3 = quad_of<ctrl>(add[3]);
+  const int at = quad_of<ctrl>(site);
+  const T v = c < 2 ? (c == 0 ? v0 : v1) : (c == 2 ? v2 : v3);
+  if (at >= 0 && c < comps) atomicAdd((T*)(field + at) + c, v);
+}
+template <typename T>
+__device__ __forceinline__ void quad_adds(Vec4<T>* field, int site, const double add[4],
+                                          int comps) {
+  const T t[4] = {(T)add[0], (T)add[1], (T)add[2], (T)add[3]};
+  quad_add<T, 0>(field, site, t, comps);
+  quad_add<T, 1>(field, site, t, comps);
+  quad_add<T, 2>(field, site, t, comps);
+  quad_add<T, 3>(field, site, t, comps);
+}
 
 // ---------------------------------------------------------------------------
 // Adjoint of one MD step (Eq. 4-8 with velocity Verlet), eight lanes per
@@ -184,33 +225,58 @@ struct AdjMDArgs {
 // through both the interpolation and the transfer.  The reads of the
 // interpolation then have adjoints
 //   j-bar_k += w_k / rho_k u-bar,   rho-bar_k -= w_k / rho_k^2 (U_k . u-bar),
-// (5.2 us per MD step of 1000 particles, a chain of loads and some 200 dependent
-// FP64 instructions; 5.9 with the squared weights' sums taken over the lanes
-// and every lane sum through LDS), which Fused adds right here (variant 1: J-bar is not read again in this
-// step); in variant 2 the read includes J, so J-bar gains the same j-bar,
-// and the adds wait for k_scatter_adjoint until every particle of the step
-// has read J-bar.
+// which are added right here, four components to a request (quad_adds).
+// In variant 2 the read includes J, so J-bar gains the same j-bar once every
+// particle of the step has read it: J-bar is the LB step's plus what abar has
+// gained.  The steps alternate between two such sums: a step reads `gin` and
+// adds to `abar`, which misses what the step before gave (to `gin`), so that
+// is added again along with it, one add where the corner is the same; the last
+// step's is the cycle's abar.  (rho-bar, which no step reads, goes to the
+// cycle's, `rbar`, at once.)  What a lane gave is kept in its own entries of
+// the step's record, which nothing reads any more: the U rows, and the site in
+// the 1/rho row.
+// Bound by a chain of loads and some 200 dependent FP64 instructions, then by
+// the requests of the adds, so four components go to a request (quad_adds).
+// One wavefront a block, as 1000 particles fill only half the CUs.  1000
+// particles in variant 2, us a step: 9.1 with J-bar itself kept up to date, by
+// a kernel of its own; 6.5 so (a sweep of 50 cycles of five steps 3430 and
+// 2900).  J-bar in two whole buffers took 6.2, but rounded more: the derivatives
+// with respect to V were off by 5.8e-8, against 5.5e-8 before and 5.3e-8 so.
 // ---------------------------------------------------------------------------
-template <typename T, bool Fused>
-__global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
-                                                           const Vec4<T>* __restrict__ jbar,
-                                                           Vec4<T>* __restrict__ abar) {
+constexpr int kAdjCouple = 64;  // one wavefront
+template <typename T, bool Reread>
+__global__ __launch_bounds__(kAdjCouple) void k_couple_adjoint(AdjMDArgs a,
+                                                               const Vec4<T>* __restrict__ jbar,
+                                                               const Vec4<T>* __restrict__ gin,
+                                                               Vec4<T>* abar, Vec4<T>* rbar) {
   const RepMD m = scalar_copy(a.md);
   const int64_t N = a.N;
   const unsigned long long t_md = (unsigned long long)a.t_md;
   const uint32_t step_lo = (uint32_t)(t_md & 0xFFFFFFFFull), step_hi = (uint32_t)(t_md >> 32);
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < N * kCornerLanes;
-       t += (int64_t)gridDim.x * kBlock) {
+  for (int64_t t = (int64_t)blockIdx.x * kAdjCouple + threadIdx.x; t < N * kCornerLanes;
+       t += (int64_t)gridDim.x * kAdjCouple) {
     const int64_t p = t / kCornerLanes;
     const int k = (int)(t & (kCornerLanes - 1));
-    const double* r = a.rec;
-    double X[3], V[3];
+    double* r = a.rec;
+    double X[3], V[3], gave[4] = {0.0, 0.0, 0.0, 0.0};
+    int gave_at = -1;
+    if (Reread && a.prev) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) gave[d] = a.prev[(6 + 3 * k + d) * N + p];
+      gave_at = (int)a.prev[(30 + k) * N + p];
+    }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       X[d] = r[d * N + p];
       V[d] = r[(3 + d) * N + p];
     }
-    if (!isfinite(X[0])) continue;  // skipped by the forward step (all 8 lanes)
+    if (!isfinite(X[0])) {  // skipped by the forward step (all 8 lanes)
+      if (Reread) {
+        quad_adds(abar, gave_at, gave, 3);
+        if (a.more) r[(30 + k) * N + p] = -1.0;
+      }
+      continue;
+    }
     Cube q;
     locate<0>(X, m.g, q);
     int cx, cy, cz, site;
@@ -224,7 +290,13 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
     const double ir = r[(30 + k) * N + p];
     const double U[3] = {r[(6 + 3 * k) * N + p], r[(7 + 3 * k) * N + p], r[(8 + 3 * k) * N + p]};
     const Vec4<T> jb = jbar[site];
-    const double jbv[3] = {(double)jb.x, (double)jb.y, (double)jb.z};
+    double jbv[3] = {(double)jb.x, (double)jb.y, (double)jb.z};
+    if (Reread && a.prev) {
+      const Vec4<T> gn = gin[site];
+      jbv[0] += (double)gn.x;
+      jbv[1] += (double)gn.y;
+      jbv[2] += (double)gn.z;
+    }
     double u[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) u[d] = group_sum<8>(w * ir * U[d]);
@@ -290,56 +362,31 @@ __global__ __launch_bounds__(kBlock) void k_couple_adjoint(AdjMDArgs a,
       for (int d = 0; d < 3; ++d) {
         a.xbar[d * N + p] = xb[d] + xs[d];
         a.vbar[d * N + p] = vb[d];
-        a.ubar[d * N + p] = ub[d];
         a.pacc[(1 + d) * N + p] += fb[d];
       }
       a.pacc[p] += gbar;
     }
-    if (Fused) {
-      T* dst = (T*)(abar + site);
-      atomicAdd(dst + 0, (T)(w * ir * ub[0]));
-      atomicAdd(dst + 1, (T)(w * ir * ub[1]));
-      atomicAdd(dst + 2, (T)(w * ir * ub[2]));
-      atomicAdd(dst + 3, (T)(-w * ir * uk));
+    double give[4];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) give[d] = w * ir * ub[d];
+    give[3] = -w * ir * uk;
+    if (Reread) {
+      if (a.more) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) r[(6 + 3 * k + d) * N + p] = give[d];
+        r[(30 + k) * N + p] = (double)site;
+      }
+      const int other = gave_at == site ? -1 : gave_at;
+      if (__any(other >= 0)) quad_adds(abar, other, gave, 3);
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        if (gave_at == site) give[d] += gave[d];
     }
-  }
-}
-
-// Variant 2: the adds of k_couple_adjoint's reads, after every particle of
-// the step has read J-bar; 32 lanes per particle (corner k = lane / 4; lanes
-// 0-2 of a corner carry j-bar components, lane 3 rho-bar).  The read
-// included the transfer field, so J-bar gains the same j-bar.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_scatter_adjoint(AdjMDArgs a, Vec4<T>* __restrict__ abar,
-                                                            Vec4<T>* __restrict__ jbar) {
-  const RepMD m = scalar_copy(a.md);
-  const int64_t N = a.N;
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < N * 32;
-       t += (int64_t)gridDim.x * kBlock) {
-    const int64_t p = t >> 5;
-    const int sl = (int)(t & 31), k = sl >> 2, c = sl & 3;
-    const double* r = a.rec;
-    double X[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) X[d] = r[d * N + p];
-    if (!isfinite(X[0])) continue;
-    Cube q;
-    locate<0>(X, m.g, q);
-    int cx, cy, cz, site;
-    stencil_site<0>(q, m.g, k, cx, cy, cz, site);
-    const double w = ((k & 1) ? q.s[0] : 1.0 - q.s[0]) * ((k & 2) ? q.s[1] : 1.0 - q.s[1]) *
-                     ((k & 4) ? q.s[2] : 1.0 - q.s[2]);
-    const double ir = r[(30 + k) * N + p];
-    T* dst = (T*)(abar + site);
-    if (c == 3) {
-      double dotv = 0.0;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) dotv += r[(6 + 3 * k + d) * N + p] * a.ubar[d * N + p];
-      atomicAdd(dst + 3, (T)(-w * ir * ir * dotv));
+    if (Reread && abar != rbar) {
+      quad_adds(abar, site, give, 3);
+      atomicAdd((T*)(rbar + site) + 3, (T)give[3]);
     } else {
-      const T val = (T)(w * ir * a.ubar[c * N + p]);
-      atomicAdd(dst + c, val);
-      atomicAdd(((T*)(jbar + site)) + c, val);
+      quad_adds(abar, site, give, 4);
     }
   }
 }
@@ -347,6 +394,18 @@ __global__ __launch_bounds__(kBlock) void k_scatter_adjoint(AdjMDArgs a, Vec4<T>
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Whether the MD steps of a cycle change the J-bar that the next one reads,
+// and the sum they then use in turn with abar: the J recorded for the cycle's
+// LB step, which only the reverse LB step at the same site reads.
+static bool rereads(const Context* c) {
+  return c->p[0].variant == 2 && c->plan.Ntot > 0 && c->plan.n_sub > 1;
+}
+template <typename T>
+static Vec4<T>* other_abar(const Context* c) {
+  const AdjState& s = c->adj;
+  return (Vec4<T>*)(s.ws + s.lay.jrec) + (size_t)s.slot * (size_t)c->plan.Stot;
+}
+
 template <typename T>
 static hipError_t lb_adjoint_t(Context* c) {
   const AdjState& s = c->adj;
@@ -360,6 +419,7 @@ static hipError_t lb_adjoint_t(Context* c) {
   a.jrec = (const Vec4<T>*)(s.ws + L.jrec) + (size_t)j * S;
   a.mrec = (const unsigned long long*)(s.ws + L.mrec) + (size_t)j * (S / 64);
   a.jbar = (Vec4<T>*)(s.ws + L.jbar);
+  a.clear = rereads(c) ? other_abar<T>(c) : nullptr;
   a.rep = (const RepLB<T>*)at(c, c->plan.lay.rep_lb);
   a.nuacc = (double*)(s.ws + L.nuacc);
   a.t_lb = (long long)s.t_lb[j];
@@ -382,12 +442,13 @@ static AdjMDArgs md_adjoint_args(Context* c) {
   const AdjLayout& L = s.lay;
   const size_t N = (size_t)c->plan.Ntot;
   AdjMDArgs a;
-  a.rec = (const double*)(s.ws + L.prec) +
+  a.rec = (double*)(s.ws + L.prec) +
           ((size_t)s.slot * c->plan.n_sub + (size_t)s.sub) * kAdjRec * N;
+  a.prev = s.sub + 1 < c->plan.n_sub ? a.rec + kAdjRec * N : nullptr;
+  a.more = s.sub > 0;
   a.fcons = (const double*)at(c, c->plan.lay.fcons);
   a.xbar = (double*)(s.ws + L.xbar);
   a.vbar = (double*)(s.ws + L.vbar);
-  a.ubar = (double*)(s.ws + L.ubar);
   a.pacc = (double*)(s.ws + L.pacc);
   a.md = (const RepMD*)at(c, c->plan.lay.rep_md);
   a.pid = (const int32_t*)at(c, c->plan.lay.pid);
@@ -401,19 +462,17 @@ static hipError_t couple_adjoint_t(Context* c) {
   const AdjMDArgs a = md_adjoint_args(c);
   Vec4<T>* jbar = (Vec4<T>*)(c->adj.ws + c->adj.lay.jbar);
   Vec4<T>* abar = (Vec4<T>*)(c->adj.ws + c->adj.lay.abar);
-  const int64_t N = a.N;
-  const dim3 grid((unsigned)((N * kCornerLanes + kBlock - 1) / kBlock));
-  if (c->p[0].variant == 1) {
-    hipLaunchKernelGGL((k_couple_adjoint<T, true>), grid, dim3(kBlock), 0, c->stream, a,
-                       (const Vec4<T>*)jbar, abar);
-    return hipGetLastError();
+  const dim3 grid((unsigned)((a.N * kCornerLanes + kAdjCouple - 1) / kAdjCouple));
+  if (rereads(c)) {
+    // (step 0, the last one reversed, adds to abar)
+    Vec4<T>* sum[2] = {abar, other_abar<T>(c)};
+    const int out = c->adj.sub & 1;
+    hipLaunchKernelGGL((k_couple_adjoint<T, true>), grid, dim3(kAdjCouple), 0, c->stream, a,
+                       (const Vec4<T>*)jbar, (const Vec4<T>*)sum[1 - out], sum[out], abar);
+  } else {
+    hipLaunchKernelGGL((k_couple_adjoint<T, false>), grid, dim3(kAdjCouple), 0, c->stream, a,
+                       (const Vec4<T>*)jbar, (const Vec4<T>*)nullptr, abar, abar);
   }
-  hipLaunchKernelGGL((k_couple_adjoint<T, false>), grid, dim3(kBlock), 0, c->stream, a,
-                     (const Vec4<T>*)jbar, abar);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scatter_adjoint<T>, dim3((unsigned)((N * 32 + kBlock - 1) / kBlock)),
-                     dim3(kBlock), 0, c->stream, a, abar, jbar);
   return hipGetLastError();
 }
 

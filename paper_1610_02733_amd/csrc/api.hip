@@ -751,7 +751,6 @@ AdjLayout adj_layout(const Context* c, int K) {
   L.abar = o; o = up(o + S * 4 * t);
   L.xbar = o; o = up(o + 3 * N * 8);
   L.vbar = o; o = up(o + 3 * N * 8);
-  L.ubar = o; o = up(o + 3 * N * 8);
   L.pacc = o; o = up(o + 4 * N * 8);
   L.nuacc = o; o = up(o + (size_t)kAdjBlocks * 4 * 8);
   L.total = o;

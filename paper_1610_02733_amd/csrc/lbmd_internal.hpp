@@ -158,8 +158,8 @@ struct AdjLayout {
   size_t prec;     // [K][n_sub][kAdjRec][Ntot] double: particle records
   size_t pbar[2];  // [19 * P] T: adjoint of the stored (post-collision) populations
   size_t jbar;     // [Stot] Vec4<T>: adjoint of the transfer field
-  size_t abar;     // [Stot] Vec4<T>: adjoint of (j, rho) read by the MD steps
-  size_t xbar, vbar, ubar;  // [3][Ntot] double
+  size_t abar;     // [Stot] Vec4<T>: adjoint of (j, rho) read by the MD steps (see k_couple_adjoint)
+  size_t xbar, vbar;  // [3][Ntot] double
   size_t pacc;     // [4][Ntot] double: per particle d/dgamma, d/df_ext
   size_t nuacc;    // [kAdjBlocks][4] double: per block d/dgamma_{bulk, shear, ghost}
   size_t total;
