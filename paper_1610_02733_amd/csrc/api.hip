@@ -250,7 +250,9 @@ int fail(Context* c, hipError_t e) {
 }
 
 // Per-replica tables and the clock, uploaded once at creation (the workspace is
-// zero, which is a single system's part_rep and the clock).
+// zero, which is a single system's part_rep and the clock).  Done on return: a
+// caller on another stream may drop the workspace or pass tensors of its own
+// right after.
 hipError_t upload_tables(Context* c) {
   const Plan& pl = c->plan;
   const int R = pl.R;
@@ -264,7 +266,12 @@ hipError_t upload_tables(Context* c) {
       lb64[r] = rep_lb<double>(c, r);
     md[r] = rep_md(c, r);
   }
-  if (R == 1) return launch_tables_one(c, lb32.data(), lb64.data(), md[0]);
+  if (R == 1) {
+    const bool f32 = pl.prec == 32;
+    const hipError_t e = launch_tables_one(c, f32 ? lb32.data() : nullptr,
+                                           f32 ? nullptr : lb64.data(), md[0]);
+    return e == hipSuccess ? hipStreamSynchronize(c->stream) : e;
+  }
   std::vector<int32_t> items(pl.item_off.begin(), pl.item_off.end());
   std::vector<int32_t> prep((size_t)std::max<int64_t>(pl.Ntot, 1), 0);
   for (int r = 0; r < R; ++r)
@@ -277,7 +284,6 @@ hipError_t upload_tables(Context* c) {
   if (e == hipSuccess) e = up_to(pl.lay.rep_md, md.data(), sizeof(RepMD) * R);
   if (e == hipSuccess) e = up_to(pl.lay.item_rep, items.data(), sizeof(int32_t) * items.size());
   if (e == hipSuccess) e = up_to(pl.lay.part_rep, prep.data(), sizeof(int32_t) * prep.size());
-  // (the sources are released on return)
   const hipError_t e2 = hipStreamSynchronize(c->stream);
   return e == hipSuccess ? e2 : e;
 }
