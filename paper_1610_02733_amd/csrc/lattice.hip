@@ -558,6 +558,40 @@ __global__ __launch_bounds__(kBlock) void k_finalize(StreamArgs<T> a,
   if (threadIdx.x == 0) totals[(size_t)rr * kRedWidth + 12] = (double)flags[0];
 }
 
+// The same sums for a single large system, in two launches: each block of the
+// first sums its share of the rows and the particles into a row of its own
+// (`Last` false), one block sums those rows.  One block alone is bound by the
+// latency of its rounds (172 us of its own at 256^3 with 1e5 particles).  The
+// whole call, us, by one block and so: 256^3 with 1e5 particles 372/236, 160^3
+// with 6e4 211/88, 200 x 190 x 180 without 141/127, 128^3 with 1e4 77/72; with
+// fewer items than fill the chip the rows behind the chunks' are too few, and
+// there is little to gain (72^3 with 3e4 79, 96^3 with 500 58).
+template <bool Last>
+__global__ __launch_bounds__(kBlock) void k_presum(const double* __restrict__ rows, int nrows,
+                                                   const double* __restrict__ v, int64_t N,
+                                                   double* __restrict__ out,
+                                                   const int32_t* __restrict__ flags) {
+  double acc[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[k] = 0.0;
+  const int stride = gridDim.x * kBlock, t0 = blockIdx.x * kBlock + threadIdx.x;
+  for (int r = t0; r < nrows; r += stride)
+#pragma unroll
+    for (int k = 0; k < (Last ? 12 : kMomentCols); ++k) acc[k] += rows[(size_t)r * kRedWidth + k];
+  if (!Last && v)
+    for (int64_t p = t0; p < N; p += stride) {
+      const double vx = v[p], vy = v[N + p], vz = v[2 * N + p];
+      acc[8] += vx;
+      acc[9] += vy;
+      acc[10] += vz;
+      acc[11] += vx * vx + vy * vy + vz * vz;
+    }
+  block_reduce_store<12>(acc, out + (size_t)blockIdx.x * kRedWidth);
+  if (Last && threadIdx.x == 0) out[12] = (double)flags[0];
+}
+constexpr int kPresumBlocks = 128;
+constexpr int64_t kPresumFrom = 4096;  // rows and particles
+
 // Items per chunk: one reduction per 4 items once there are enough chunks to
 // fill the chip several times over; at most max_rows chunks.
 static int moment_chunk(int nitems, int max_rows) {
@@ -588,6 +622,19 @@ static hipError_t moments_t(Context* c, int rep, void* d_rho, void* d_u, double*
   const int per = moment_chunk(a.nitems, a.nitems);
   const hipError_t e = moments_launch<T>(c, a, per, rep, d_rho, d_u, partials);
   if (e != hipSuccess || !d_totals) return e;
+  const int rows = (a.nitems + per - 1) / per;
+  // (the first launch's rows go behind the chunks', which leave most of the
+  // region free once a chunk is several items)
+  if (c->plan.R == 1 && rows + c->plan.Ntot >= kPresumFrom && a.nitems - rows >= kPresumBlocks) {
+    const double* v = (const double*)(c->bound ? c->v : nullptr);
+    const int32_t* flags = (const int32_t*)at(c, c->plan.lay.flags);
+    double* sums = partials + (size_t)rows * kRedWidth;
+    hipLaunchKernelGGL(k_presum<false>, dim3(kPresumBlocks), dim3(kBlock), 0, c->stream, partials,
+                       rows, v, c->plan.Ntot, sums, flags);
+    hipLaunchKernelGGL(k_presum<true>, dim3(1), dim3(kBlock), 0, c->stream, sums, kPresumBlocks,
+                       (const double*)nullptr, (int64_t)0, d_totals, flags);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_finalize<T>, dim3(c->plan.R), dim3(kBlock), 0, c->stream, a,
                      (const RepMD*)at(c, c->plan.lay.rep_md), partials,
                      (const double*)(c->bound ? c->v : nullptr), c->plan.Ntot, d_totals, per,
